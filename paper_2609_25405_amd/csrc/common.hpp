@@ -102,7 +102,8 @@ struct GemmArgs {
     int b_blocked;
     // 1: the launch runs concurrently with another stream's launches, so the workgroup time it
     // takes from the shared CUs, not its own length, is what it costs; the bf16 dispatch then
-    // gives split-K projections of 129..256 rows the largest tiles
+    // gives split-K projections of 129..256 rows the largest tiles, and larger ones tiles that
+    // leave registers and LDS to that stream's small kernels
     int wide;
 };
 hipError_t launch_gemm(int dtype, int epilogue, const GemmArgs &a, hipStream_t s);
@@ -111,7 +112,7 @@ hipError_t launch_block_weights(const void *src, void *dst, int rows, int cols, 
 // split-K factor (<= max_splits; each split a run of whole 64-deep stages, the stages dealt as
 // evenly as the count allows) for a bf16 residual-add projection of this shape; launch_gemm
 // ignores a requested split count larger than K's number of stages
-int gemm_add_splits(int M, int N, int K, int max_splits);
+int gemm_add_splits(int M, int N, int K, int max_splits, bool wide);
 
 // LoRA shrink: u[row][j*r + k] = scale[j] * sum_i x[row][i] a_j[k][i] for the adapter j of the
 // row (row_adapter[row]), 0 in the other adapters' columns.  x [rows][K] with row stride ldx,

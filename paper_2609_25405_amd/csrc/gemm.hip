@@ -13,7 +13,8 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.hpp"
+#include "gemm_big.hpp"
+#include "gemm_common.hpp"
 #include "orthrus.h"
 
 namespace orthrus {
@@ -21,30 +22,6 @@ namespace orthrus {
 namespace {
 
 constexpr int BK = 64;
-
-__device__ __forceinline__ float silu(float g) { return g / (1.f + __expf(-g)); }
-
-// 16-byte global -> LDS copy: lane i of the wave writes lds + 16 * i (lds is wave-uniform).
-// AUX is the cache policy: 0 default, kNonTemporal for data the launch reads exactly once.
-constexpr int kNonTemporal = 2;
-template <int AUX = 0>
-__device__ __forceinline__ void copy16_to_lds(const void *src, char *lds) {
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds, 16, 0, AUX);
-}
-
-// s_waitcnt immediate that waits until at most n vector-memory operations are outstanding
-// (gfx9 encoding: vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14; expcnt and lgkmcnt at
-// their maxima so they impose no wait)
-template <int N>
-constexpr int vmcnt_imm() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    return (N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8);
-}
-
-// workgroup barrier for the LDS ring: the LDS reads issued before it have completed and no
-// memory access moves across it; unlike __syncthreads it does not drain the outstanding
-// global->LDS copies of later stages (their completion is awaited explicitly with vmcnt)
-__device__ __forceinline__ void ring_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // STREAM_B: the launch has one row tile, so each weight byte is read exactly once; its copies
 // are non-temporal (LM head 64 x 32000 x 4096 in the step: 66 -> 56 us)
@@ -548,14 +525,17 @@ hipError_t run_bf16(const GemmArgs &a, hipStream_t s) {
 //    workgroups) with a 4-deep copy ring keep enough bytes in flight per CU (LM head
 //    64 x 32000 x 4096: 70 -> 43 us with warm caches; decode-batch QKV 35 -> 25 us); gate/up
 //    on 64x128 tiles (224 workgroups instead of 112: 58.6 -> 43.9 us with cold weights);
-//  - gate/up above 896 rows: 192x256 or 256x256 tiles over 8 waves, whichever needs fewer
+//  - every projection above 896 rows that has the chip to itself: the kernel of gemm_big.hip;
+//    beside another stream's launches (GemmArgs::wide) it leaves no registers and no LDS for that
+//    stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against 5.99 ms), and
+//    the kernel of this file stays;
+//  - gate/up above 896 rows (wide): 192x256 or 256x256 tiles over 8 waves, whichever needs fewer
 //    rounds of workgroups times tile rows;
 //  - gate/up of 129..256 rows: one 256x128 row tile, the weights streamed once (non-temporal)
 //    through 3-deep rings (M = 256 with cold weights: 110 -> 71 us against 128x128 tiles);
-//  - residual-add projections of M > 896 rows: 256x256 tiles over 8 waves with the split-K
-//    count gemm_add_splits picks (o 58 -> 46 us, down 177 -> 135 us against 128x128 tiles at
-//    M = 1088; down at M = 1568 264 -> 195 us, at M = 2048 275 -> 211 us against 192x256
-//    tiles split 2, whose 288 or 352 workgroups spill into a second round);
+//  - residual-add projections of M > 896 rows (wide): 256x256 tiles over 8 waves with the
+//    split-K count gemm_add_splits picks (o 58 -> 46 us, down 177 -> 135 us against 128x128
+//    tiles at M = 1088);
 //  - otherwise 128x128 (64 KiB of LDS, two workgroups per CU hide each other's waits).
 //  - medium M (64 < M <= 896: decode-heavy and small mixed batches, where the weights stream):
 //    more, smaller workgroups and deeper split-K for the residual-add projections (down at
@@ -578,6 +558,7 @@ hipError_t run_bf16(const GemmArgs &a, hipStream_t s) {
 //    M = 512 147 against 174 us, M = 896 240 against 256 us).
 template <int EPI>
 hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
+    const bool big = !a.wide && gemm_big_takes(a);
     if constexpr (EPI == EPI_QKV_ROPE) {
         if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 512) return run_bf16<64, 128, 1, 4, EPI, 64, 3>(a, s);
@@ -586,9 +567,10 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 256) return run_bf16<256, 128, 4, 2, EPI, 64, 3, 3, true>(a, s);
+        if (big && a.M > 896) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, true, 1), s);
         if (a.M > 896) {
             // the row tile whose rounds of workgroups over 256 CUs cost least, a round costing
-            // its tile's rows (M = 1024: 256x256 tiles, two rounds, 211 against 242 us)
+            // its tile's rows
             const long t192 = (long)((a.M + 191) / 192) * ((a.N + 127) / 128);
             const long t256 = (long)((a.M + 255) / 256) * ((a.N + 127) / 128);
             if ((t256 + 255) / 256 * 256 < (t192 + 255) / 256 * 192) return run_bf16<256, 256, 2, 4, EPI>(a, s);
@@ -612,10 +594,12 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         if (split && a.wide && a.M > 128 && a.M <= 256) return run_bf16<256, 256, 2, 4, EPI>(a, s);
         if (split && a.M <= 256) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, false>(a, s);
         if (split && a.M <= 896) return run_bf16<128, 128, 2, 2, EPI>(a, s);
+        if (big && EPI == EPI_ADD_F32 && a.partial && a.M > 896) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, false, a.splits), s);
         if (EPI == EPI_ADD_F32 && a.partial && a.M > 896) return run_bf16<256, 256, 2, 4, EPI>(a, s);
         if (EPI == EPI_ADD_F32) return run_bf16<128, 128, 4, 2, EPI>(a, s);
-        // fp32 rows of a large QKV projection (rotated by a row kernel): one round of big tiles
-        if (a.M > 1280) return a.M <= 1728 ? run_bf16<192, 256, 2, 4, EPI>(a, s) : run_bf16<256, 256, 2, 4, EPI>(a, s);
+        // fp32 rows of a large QKV projection (rotated by a row kernel)
+        if (big && a.M > 1280) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, false, 1), s);
+        if (a.M > 1280) return run_bf16<256, 256, 2, 4, EPI>(a, s);
         return run_bf16<128, 128, 2, 2, EPI>(a, s);
     }
 }
@@ -629,14 +613,13 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
 //    the smaller one on a tie;
 //  - 64 < M <= 896, from measurements of the 7B projections: 4 up to M = 640 (64x64 or 128x128
 //    tiles; weight streaming wants many workgroups), then 2;
-//  - M > 896 (256x256 tiles, one workgroup per CU): the factor with the least (rounds of
-//    workgroups over 256 CUs) x (stages per split), the smaller one on a tie.  The copies of a
-//    round's stages bound these launches, so a second round that is only partly full costs as
-//    much as the first (M = 1568: split 2 fills one round with 224 workgroups).
-int gemm_add_splits(int M, int N, int K, int max_splits) {
-    const int stages = K / BK;
+//  - M > 896: the factor whose cover of the output (plan_big) and slabs take least time; beside
+//    another stream's launches (wide) the factor with the least (rounds of workgroups over 256
+//    CUs) x (stages per split), the smaller one on a tie.
+int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
     auto valid = [&](int s) { return s <= max_splits && K % BK == 0 && K / s >= 512; };
-    if (M > 896) {
+    if (M > 896 && wide) {
+        const int stages = K / BK;
         const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
         int best = 1;
         long best_cost = -1;
@@ -644,6 +627,18 @@ int gemm_add_splits(int M, int N, int K, int max_splits) {
             if (s > 1 && !valid(s)) continue;
             const long cost = (tiles * s + 255) / 256 * ((stages + s - 1) / s);
             if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
+        }
+        return best;
+    }
+    if (M > 896) {
+        int best = 1;
+        double best_cost = 0.0;
+        for (int s = 1; s <= max_splits; ++s) {
+            if (s > 1 && !valid(s)) continue;
+            // a slab is written here and read by the next row kernel: 8 bytes per value at about
+            // 4 TB/s, in stage times of 1.45 us
+            const double cost = plan_big(M, N, K, false, s).cost + s * ((double)M * N * 8 / 4e6 / 1.45);
+            if (best_cost == 0.0 || cost < best_cost) { best = s; best_cost = cost; }
         }
         return best;
     }

@@ -1,0 +1,420 @@
+// The large projections of the step (bf16, more than a few hundred rows): C[M][N] = A[M][K] *
+// W[N][K]^T on tiles of 256 rows x 256 weight rows, with the same epilogues as the small ones.
+//
+// What bounds them is power: at these sizes the chip holds its clock only as far as the energy of
+// the MFMAs, of the LDS reads and of the copies allows (ablated at 1024 x 28672 x 4096: MFMAs
+// alone 133 us, with their LDS reads 151 us, with the copies 187-198 us).  Hence:
+//  - v_mfma_f32_16x16x32_bf16 instead of 32x32x16: the same flops at half the accumulator
+//    traffic, 2.05 against 1.80 PFLOP/s in a stream of MFMAs on random operands (2.05 against
+//    1.82 GHz); two waves per SIMD, because one wave alone issues it every 19 cycles instead
+//    of 16;
+//  - 64 x 128 outputs per wave, the fewest LDS bytes per flop that two waves per SIMD allow;
+//  - no bubble at a stage's barrier: the fragments of k-step i + 1 are read under the MFMAs of
+//    k-step i across stages too, the barrier sits between the stage's two k-steps, and each copy
+//    is issued between two MFMAs, with the row offsets in registers and the stage's offset in a
+//    scalar (buffer loads to LDS), so a copy costs no vector instruction;
+//  - rings of two activation and three weight stages (all 160 KB of LDS): the weights come from
+//    HBM or the last-level cache and are requested three stages ahead, the activations sit in L2.
+// Together (1024-row gate/up 238 -> 197 us, down 114 -> 94 us, QKV 58 -> 46 us; 2048-row gate/up
+// 463 -> 390 us, all with cold weights).
+//
+// A launch covers its output with 256 x 256 tiles and, where their last round over the 256 CUs
+// would be nearly empty, gives some columns or the last rows to a second, smaller tile shape
+// (see plan_big).
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+#include <vector>
+
+#include "gemm_common.hpp"
+#include "gemm_big.hpp"
+
+namespace orthrus {
+
+namespace {
+
+constexpr int kBK = 64;          // K depth of a stage: one 128-byte line per row
+constexpr int kRowBytes = kBK * 2;
+constexpr int kWaves = 8;
+constexpr int kRingA = 2, kRingB = 3;
+constexpr int kLds = 160 * 1024;
+typedef __attribute__((address_space(3))) void lds_void;
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// rows of a matrix as a buffer: reads past `bytes` return zero
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_buffer(const void *p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (unsigned)bytes, 0x00020000);
+}
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// One BM x BN tile (BN weight rows; SwiGLU: BN / 2 gate and as many up rows) over K stages
+// [kt0, kt0 + nk).  WM x WN waves.
+template <int BM, int BN, int WM, int WN, int EPI>
+__device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, int n0, int kt0, int nk, int split,
+                                         int splits) {
+    static_assert(WM * WN == kWaves, "eight waves");
+    constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
+    constexpr bool SW = EPI == EPI_SWIGLU;
+    constexpr int A_INST = BM / (8 * kWaves), B_INST = BN / (8 * kWaves), INST = A_INST + B_INST;
+    constexpr int ABUF = BM * kRowBytes, BBUF = BN * kRowBytes, B_BASE = kRingA * ABUF;
+    static_assert(A_INST * 8 * kWaves == BM && B_INST * 8 * kWaves == BN, "copies divide over the waves");
+    static_assert(kRingA * ABUF + kRingB * BBUF <= kLds && TM % 16 == 0 && TN % 16 == 0, "tile");
+    static_assert(!SW || (FN % 2 == 0 && TN % 16 == 0), "gate and up halves of a wave");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+
+    // LDS row r holds 16-byte chunk c at physical chunk c ^ key(r): the 16 lanes of one pass of a
+    // fragment read (16 consecutive rows, same chunk) hit 16 distinct 16-byte bank groups.  Lane l
+    // of a copy writes row r0 + l / 8 at physical chunk l % 8 and fetches the chunk stored there.
+    auto key_of = [](int row) { return (row / 2) % 8; };
+    const size_t lda_b = (size_t)a.lda * 2, ldb_b = (size_t)a.K * 2;
+    // the tile's rows of A and of the weights as buffers: rows past M or N read as zero
+    const int b_cols = SW ? BN / 2 : BN;
+    const int b_valid = min(b_cols, a.N - n0);
+    const __amdgpu_buffer_rsrc_t ra = rows_buffer((const char *)a.A + (size_t)m0 * lda_b, (size_t)min(BM, a.M - m0) * lda_b);
+    // the 64 x 64 blocked copy is padded to whole blocks
+    const size_t b_bytes = (size_t)(a.b_blocked ? (b_valid + 63) / 64 * 64 : b_valid) * ldb_b;
+    const __amdgpu_buffer_rsrc_t rb0 = rows_buffer((const char *)a.B0 + (size_t)n0 * ldb_b, b_bytes);
+    const __amdgpu_buffer_rsrc_t rb1 = rows_buffer((const char *)(SW ? a.B1 : a.B0) + (size_t)n0 * ldb_b, b_bytes);
+    const int b_stage = a.b_blocked ? 64 * kRowBytes : kRowBytes;   // bytes between K stages of a weight row
+    unsigned avo[A_INST], bvo[B_INST];
+#pragma unroll
+    for (int i = 0; i < A_INST; ++i) {
+        const int row = 8 * (kWaves * i + wave) + lane / 8;
+        avo[i] = row * (unsigned)lda_b + ((lane % 8) ^ key_of(row)) * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < B_INST; ++i) {
+        const int row = 8 * (kWaves * i + wave) + lane / 8;
+        const int src = SW ? row / TN * (TN / 2) + row % (TN / 2) : row;
+        const unsigned at = a.b_blocked ? (src / 64 * (a.K / 64) * 64 + src % 64) * kRowBytes : src * (unsigned)ldb_b;
+        bvo[i] = at + ((lane % 8) ^ key_of(row)) * 16;
+    }
+    auto copy_a = [&](int i, int kt, int buf) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(smem + buf * ABUF + (kWaves * i + wave) * 1024), 16,
+                                                 avo[i], (kt0 + kt) * kRowBytes, 0, 0);
+    };
+    auto copy_b = [&](int i, int kt, int buf) {
+        // the eight rows of one copy lie in one half of a wave's slice
+        const bool up = SW && (8 * (kWaves * i + wave)) % TN >= TN / 2;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(up ? rb1 : rb0,
+                                                 (lds_void *)(smem + B_BASE + buf * BBUF + (kWaves * i + wave) * 1024), 16,
+                                                 bvo[i], (kt0 + kt) * b_stage, 0, 0);
+    };
+
+    // D = W-fragment x A-fragment: lane holds row (lane & 15) of A and four consecutive weight
+    // rows 4 (lane / 16) + r, i.e. four consecutive output columns
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int arow = wm * TM + (lane & 15), brow = wn * TN + (lane & 15);
+    int aoff[2], boff[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        const int chunk = kk * 4 + (lane >> 4);
+        aoff[kk] = arow * kRowBytes + ((chunk ^ key_of(arow)) << 4);
+        boff[kk] = B_BASE + brow * kRowBytes + ((chunk ^ key_of(brow)) << 4);
+    }
+    bf16x8 fa[2][FM], fb[2][FN];
+    // fragment i (A fragments first) of k-step kk into register set kk
+    auto read1 = [&](int i, int kk, const char *sa, const char *sb) {
+        if (i < FM) fa[kk][i] = *(const bf16x8 *)(sa + aoff[kk] + i * 16 * kRowBytes);
+        else fb[kk][i - FM] = *(const bf16x8 *)(sb + boff[kk] + (i - FM) * 16 * kRowBytes);
+    };
+    const bool live = m0 + wm * TM < a.M;   // some row of this wave exists
+
+    // prologue: A stages 0, 1 and weight stages 0, 1, 2 in flight; the first k-step's fragments
+#pragma unroll
+    for (int st = 0; st < kRingB; ++st) {
+        if (st < kRingA) {
+#pragma unroll
+            for (int i = 0; i < A_INST; ++i) copy_a(i, min(st, nk - 1), st);
+        }
+#pragma unroll
+        for (int i = 0; i < B_INST; ++i) copy_b(i, min(st, nk - 1), st);
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm<INST + B_INST>());
+    ring_barrier();
+    if (live) {
+#pragma unroll
+        for (int i = 0; i < FM + FN; ++i) read1(i, 0, smem, smem);
+    }
+    SCHED_FENCE();
+    // Stage kt: the MFMAs of its first k-step over the reads of its second; then everyone's copies
+    // of stage kt + 1 have landed (only the B_INST copies of weight stage kt + 2 may be left) and
+    // everyone has read all of stage kt; then the MFMAs of the second k-step over the first reads of
+    // stage kt + 1 and the copies of A stage kt + 2 and weight stage kt + 3 into the buffers just
+    // freed.  Copies past the last stage repeat it, so that every iteration issues the same count.
+    int ab = 0, bb = 0;
+    auto k_loop = [&](auto live_c) {
+        constexpr bool L = decltype(live_c)::value;
+        for (int kt = 0; kt < nk; ++kt) {
+            const int an = ab ^ 1, bn = bb == kRingB - 1 ? 0 : bb + 1;
+            const int kta = min(kt + kRingA, nk - 1), ktb = min(kt + kRingB, nk - 1);
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                if (kk == 1) {
+                    SCHED_FENCE();
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm<B_INST>());
+                    ring_barrier();
+                    SCHED_FENCE();
+                }
+                const char *sa = smem + (kk ? an : ab) * ABUF, *sb = smem + (kk ? bn : bb) * BBUF;
+                if (!L) {
+                    if (kk == 1) {
+#pragma unroll
+                        for (int i = 0; i < A_INST; ++i) copy_a(i, kta, ab);
+#pragma unroll
+                        for (int i = 0; i < B_INST; ++i) copy_b(i, ktb, bb);
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                    for (int nj = 0; nj < FN; ++nj) {
+                        const int i = mi * FN + nj, ni = (mi & 1) ? FN - 1 - nj : nj;
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][ni], fa[kk][mi], acc[mi][ni], 0, 0, 0);
+                        if (i < FM + FN) read1(i, kk ^ 1, sa, sb);
+                        if (kk == 1) {
+                            if (i < A_INST) copy_a(i, kta, ab);
+                            else if (i < INST) copy_b(i - A_INST, ktb, bb);
+                        }
+                        SCHED_FENCE();
+                    }
+            }
+            ab = an;
+            bb = bn;
+        }
+    };
+    static_assert(FM * FN >= FM + FN && FM * FN >= INST, "an MFMA for every read and copy");
+    if (live) k_loop(std::true_type{});
+    else k_loop(std::false_type{});
+    // the repeated copies of the last iterations still write LDS: drain them before the epilogue
+    // reuses the buffers
+    __builtin_amdgcn_s_waitcnt(0);
+
+    // LoRA update: acc += U B^T for rows below lora.rows (split 0), 32 columns of U per MFMA step
+    // (U as its bf16 rounding plus remainder, two MFMAs), operands straight from global memory; a
+    // fragment's 8 columns lie in one adapter's block because ranks are multiples of 16
+    if (a.lora.n > 0 && split == 0 && m0 < a.lora.rows) {
+        const LoraGemm &L = a.lora;
+        const int ldu = L.n * L.r;
+        const bf16x8 zero = {};
+        for (int c0 = 0; c0 < ldu; c0 += 32) {
+            const int c = c0 + 8 * (lane >> 4);
+            const bool in = c < ldu;
+            const int j = in ? c / L.r : 0, kk = in ? c % L.r : 0;
+            bf16x8 ua[FM], ul[FM];
+#pragma unroll
+            for (int mi = 0; mi < FM; ++mi) {
+                const int row = m0 + wm * TM + mi * 16 + (lane & 15);
+                const bool ok = in && row < L.rows;
+                ua[mi] = ok ? *(const bf16x8 *)((const bf16 *)L.u + (size_t)row * ldu + c) : zero;
+                ul[mi] = ok ? *(const bf16x8 *)((const bf16 *)L.u_lo + (size_t)row * ldu + c) : zero;
+            }
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) {
+                int col;
+                const bf16 *src;
+                if constexpr (SW) {
+                    col = n0 + wn * (TN / 2) + (ni % (FN / 2)) * 16 + (lane & 15);
+                    src = (const bf16 *)(ni < FN / 2 ? L.b0[j] : L.b1[j]);
+                } else {
+                    col = n0 + wn * TN + ni * 16 + (lane & 15);
+                    src = (const bf16 *)L.b0[j];
+                }
+                const bf16x8 ub = in ? *(const bf16x8 *)(src + (size_t)min(col, a.N - 1) * L.r + kk) : zero;
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi) {
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub, ua[mi], acc[mi][ni], 0, 0, 0);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub, ul[mi], acc[mi][ni], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    if constexpr (SW) {
+        // the bf16 output tile through LDS, so that its rows leave as whole 16-byte pieces
+        constexpr int OC = BN / 2, OROW = OC * 2 + 16;
+        static_assert(BM * OROW <= kLds, "output tile");
+        __syncthreads();
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < FN / 2; ++ni) {
+                const f32x4 g = acc[mi][ni], u = acc[mi][ni + FN / 2];
+                const int row = wm * TM + mi * 16 + (lane & 15), col = wn * (TN / 2) + ni * 16 + (lane >> 4) * 4;
+                *(uint2 *)(smem + row * OROW + col * 2) =
+                    uint2{pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]), pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3])};
+            }
+        __syncthreads();
+        constexpr int PPR = OC / 8;
+        for (int c = threadIdx.x; c < BM * PPR; c += 64 * kWaves) {
+            const int row = c / PPR, part = c % PPR, grow = m0 + row, gcol = n0 + part * 8;
+            if (grow < a.M && gcol < a.N)
+                *(u32x4 *)((bf16 *)a.out + (size_t)grow * a.ldo + gcol) = *(const u32x4 *)(smem + row * OROW + part * 16);
+        }
+        return;
+    }
+    // fp32 rows: stored, added into the residual stream, or this split's share into its own slab.
+    // 16-byte stores where the rows allow them
+    float *base = splits > 1 ? a.partial + (size_t)split * a.split_stride : (float *)a.out;
+    const bool add = EPI == EPI_ADD_F32 && splits == 1;
+    const bool vec = a.ldo % 4 == 0 && (uintptr_t)base % 16 == 0;
+#pragma unroll
+    for (int mi = 0; mi < FM; ++mi) {
+        const int row = m0 + wm * TM + mi * 16 + (lane & 15);
+        if (row >= a.M) continue;
+        float *o = base + (size_t)row * a.ldo;
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni) {
+            const int col = n0 + wn * TN + ni * 16 + (lane >> 4) * 4;
+            if (vec && col + 3 < a.N) {
+                f32x4 v = acc[mi][ni];
+                if (add) v += *(const f32x4 *)(o + col);
+                *(f32x4 *)(o + col) = v;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (col + r < a.N) o[col + r] = (add ? o[col + r] : 0.f) + acc[mi][ni][r];
+            }
+        }
+    }
+}
+#endif
+
+// block b of n in XCD-contiguous order: blocks are dealt round-robin to the 8 XCDs, and each
+// XCD walks a run of consecutive tiles (row tiles fastest), so re-reads stay inside one L2
+__device__ __forceinline__ int xcd_run(int b, int n) {
+    const int x = b % 8, q = n / 8, r = n % 8;
+    return x * q + min(x, r) + b / 8;
+}
+
+// Blocks [0, main * splits): 256 x 256 tiles over row tiles [0, m_main) and the first n_main column
+// tiles; the rest: tiles of the second shape over the remaining columns (of every row) or rows.
+template <int EPI, int BM2, int BN2, int WM2, int WN2>
+__global__ __launch_bounds__(64 * kWaves, 1) void gemm_big_kernel(GemmArgs a, BigPlan p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __shared__ __attribute__((aligned(1024))) char smem[kLds];
+    constexpr int C1 = EPI == EPI_SWIGLU ? 128 : 256, C2 = EPI == EPI_SWIGLU ? BN2 / 2 : BN2;
+    const int n1 = p.m_main * p.n_main, n2 = p.m_alt * p.n_alt, stages = a.K / kBK;
+    int b = blockIdx.x;
+    if (b < n1 * p.splits) {
+        const int split = b / n1, t = xcd_run(b % n1, n1);
+        const int kt0 = (int)((long)split * stages / p.splits), kt1 = (int)((long)(split + 1) * stages / p.splits);
+        big_tile<256, 256, 4, 2, EPI>(a, smem, t % p.m_main * 256, t / p.m_main * C1, kt0, kt1 - kt0, split, p.splits);
+        return;
+    }
+    if constexpr (BM2 > 0) {
+        b -= n1 * p.splits;
+        const int split = b / n2, t = xcd_run(b % n2, n2);
+        const int kt0 = (int)((long)split * stages / p.splits), kt1 = (int)((long)(split + 1) * stages / p.splits);
+        big_tile<BM2, BN2, WM2, WN2, EPI>(a, smem, p.row_alt + t % p.m_alt * BM2, p.col_alt + t / p.m_alt * C2, kt0, kt1 - kt0,
+                                          split, p.splits);
+    }
+#endif
+}
+
+// time of the last of n1 tiles of cost c1, then n2 of cost c2, handed in order to 256 CUs as
+// they become free
+double makespan(long n1, double c1, long n2, double c2) {
+    std::vector<std::pair<double, long>> busy{{0.0, 256}};   // (free at, CUs), ascending
+    double last = 0.0;
+    auto deal = [&](long n, double c) {
+        while (n > 0) {
+            const auto [t, k] = busy.front();
+            const long take = std::min(n, k);
+            if (take == k) busy.erase(busy.begin());
+            else busy.front().second -= take;
+            const std::pair<double, long> done{t + c, take};
+            busy.insert(std::upper_bound(busy.begin(), busy.end(), done), done);
+            last = std::max(last, t + c);
+            n -= take;
+        }
+    };
+    deal(n1, c1);
+    deal(n2, c2);
+    return last;
+}
+
+}  // namespace
+
+BigPlan plan_big(int M, int N, int K, bool swiglu, int splits) {
+    const int C = swiglu ? 128 : 256;
+    const int mt = (M + 255) / 256, nt = (N + C - 1) / C;
+    const double stages = (double)K / kBK / splits;
+    // cost of a tile in stage times of a 256 x 256 tile, prologue and epilogue included
+    const double c256 = stages + 4.0, c192 = 0.79 * stages + 3.5, c128 = 0.60 * stages + 3.0;
+    BigPlan best;
+    best.m_main = mt;
+    best.n_main = nt;
+    best.splits = splits;
+    best.cost = makespan((long)mt * nt * splits, c256, 0, 0.0);
+    auto offer = [&](const BigPlan &p) {
+        if (p.cost < best.cost * 0.98) best = p;
+    };
+    // the last rows on 128-row tiles
+    const int rem = M % 256;
+    if (rem > 0 && rem <= 128) {
+        BigPlan p;
+        p.shape = 1;
+        p.m_main = M / 256;
+        p.n_main = p.m_main ? nt : 0;
+        p.m_alt = 1;
+        p.n_alt = nt;
+        p.row_alt = M - rem;
+        p.splits = splits;
+        p.cost = makespan((long)p.m_main * p.n_main * splits, c256, (long)nt * splits, c128);
+        offer(p);
+    }
+    // columns past the first j column tiles on 192- or 128-wide tiles
+    for (int shape = 2; shape <= 3; ++shape) {
+        const int w = (shape == 2 ? 192 : 128) / (swiglu ? 2 : 1);
+        for (int j = 0; j < nt; ++j) {
+            BigPlan p;
+            p.shape = shape;
+            p.m_main = mt;
+            p.n_main = j;
+            p.m_alt = mt;
+            p.n_alt = (N - j * C + w - 1) / w;
+            p.col_alt = j * C;
+            p.splits = splits;
+            p.cost = makespan((long)mt * j * splits, c256, (long)mt * p.n_alt * splits, shape == 2 ? c192 : c128);
+            offer(p);
+        }
+    }
+    return best;
+}
+
+template <int EPI>
+static hipError_t launch_shape(const GemmArgs &a, const BigPlan &p, hipStream_t s) {
+    const dim3 grid((p.m_main * p.n_main + p.m_alt * p.n_alt) * p.splits), block(64 * kWaves);
+    switch (p.shape) {
+        case 0: hipLaunchKernelGGL((gemm_big_kernel<EPI, 0, 0, 4, 2>), grid, block, 0, s, a, p); break;
+        case 1: hipLaunchKernelGGL((gemm_big_kernel<EPI, 128, 256, 2, 4>), grid, block, 0, s, a, p); break;
+        case 2: hipLaunchKernelGGL((gemm_big_kernel<EPI, 256, 192, 4, 2>), grid, block, 0, s, a, p); break;
+        default: hipLaunchKernelGGL((gemm_big_kernel<EPI, 256, 128, 4, 2>), grid, block, 0, s, a, p); break;
+    }
+    return hipGetLastError();
+}
+
+// a tile's 256 rows are addressed by 32-bit byte offsets
+bool gemm_big_takes(const GemmArgs &a) {
+    return a.K > 0 && a.K % kBK == 0 && (size_t)a.lda * 2 * 256 <= 0x7fffffffu && (size_t)a.K * 2 * 256 <= 0x7fffffffu;
+}
+
+hipError_t launch_gemm_big(int epi, const GemmArgs &a, const BigPlan &p, hipStream_t s) {
+    if (!gemm_big_takes(a) || a.K / kBK < p.splits || (p.splits > 1 && (epi != EPI_ADD_F32 || !a.partial)))
+        return hipErrorInvalidValue;
+    switch (epi) {
+        case EPI_STORE_F32: return launch_shape<EPI_STORE_F32>(a, p, s);
+        case EPI_ADD_F32: return launch_shape<EPI_ADD_F32>(a, p, s);
+        case EPI_SWIGLU: return launch_shape<EPI_SWIGLU>(a, p, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace orthrus

@@ -1,0 +1,23 @@
+// Interface of the large bf16 projections (gemm_big.hip).
+#pragma once
+
+#include "common.hpp"
+
+namespace orthrus {
+
+// How a launch covers its output: 256 x 256 tiles on m_main x n_main of it and m_alt x n_alt tiles
+// of a second shape from (row_alt, col_alt) on; columns count outputs.
+struct BigPlan {
+    int shape = 0;    // second shape: 0 none, 1 128 x 256 (last rows), 2 256 x 192, 3 256 x 128 (last columns)
+    int m_main = 0, n_main = 0, m_alt = 0, n_alt = 0, row_alt = 0, col_alt = 0;
+    int splits = 1;
+    double cost = 0;  // estimated length in stage times of a 256 x 256 tile
+};
+// the cover of [M][N] (swiglu: N gate and N up rows of weights) with the least estimated length
+BigPlan plan_big(int M, int N, int K, bool swiglu, int splits);
+// whether the kernel's addressing covers these operands (K % 64 == 0, rows of at most 8 MB)
+bool gemm_big_takes(const GemmArgs &a);
+// EPI_STORE_F32, EPI_ADD_F32 (with plan.splits > 1: slabs in a.partial) or EPI_SWIGLU
+hipError_t launch_gemm_big(int epi, const GemmArgs &a, const BigPlan &p, hipStream_t s);
+
+}  // namespace orthrus

@@ -515,6 +515,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ga.ldo = ldo;
         ga.splits = 1;
         ga.lora = lg;
+        ga.wide = concurrent;
         return launch_gemm(dt, epi, ga, g.st);
     };
     // residual-add projection into x; bf16: split K when the tile count is low and leave the
@@ -522,7 +523,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     // row group and used by every group, so the pending slab count is the same for all rows.
     int max_rows = 0;
     for (int gi = 0; gi < n_groups; ++gi) max_rows = std::max(max_rows, groups[gi].r1 - groups[gi].r0);
-    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits) : 1; };
+    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits, concurrent) : 1; };
     auto add_proj = [&](const Group &g, const char *A, int lda, const void *B, int K, int splits,
                         const LoraGemm &lg) -> hipError_t {
         GemmArgs ga{};

@@ -1,0 +1,46 @@
+"""Projections of more than 896 rows (the 256-row tiles of the large kernel and its second tile
+shapes) against the float64 oracle, at row counts on and beside the edges of its tiles: one row past
+the smallest batch it takes, a last row tile of one row, of exactly 128 and of 129 rows, whole
+tiles, and enough rows for several rounds; with LoRA adapters on part of the rows (ranks 16 and 48,
+so that a 32-column step of the update ends inside and past an adapter's block)."""
+import numpy as np
+import pytest
+import torch
+
+from tests.parity import Pair
+from workload import Batch, DecodeRow, EmbChunk, ModelConfig, PagedKV, draw_tokens, make_lora, make_weights
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _need_gpu(request):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"\n[case] {request.node.name}", flush=True)
+
+
+@pytest.mark.parametrize("rows,rank", [(897, 0), (1025, 0), (1152, 16), (1281, 48), (1536, 0), (2049, 0)])
+def test_rows(rows, rank):
+    cfg = ModelConfig(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=2816, vocab=512,
+                      dtype="bf16")
+    W = make_weights(cfg, 11)
+    if rank:
+        W["adapters"] = [make_lora(cfg, 5, rank, tag=i) for i in range(2)]
+    n_dec = 3
+    lens, left = [], rows - n_dec
+    while left:
+        lens.append(min(left, 300))
+        left -= lens[-1]
+    kv = PagedKV(cfg, sum(-(-n // 16) for n in lens) + n_dec * 8 + 4, len(lens) + n_dec, 20, 3)
+    for i, n in enumerate(lens):
+        kv.reserve(i, n)
+    for j in range(n_dec):
+        kv.fill_random(len(lens) + j, 40 + j, 9)
+        kv.reserve(len(lens) + j, 41 + j)
+    batch = Batch([EmbChunk(i, 0, n, True, "mean") for i, n in enumerate(lens)],
+                  [DecodeRow(len(lens) + j, 40 + j) for j in range(n_dec)], draw_tokens(7, 0, rows, cfg.vocab),
+                  chunk_adapter=[(i % 3) - 1 for i in range(len(lens))] if rank else None)
+    pair = Pair(cfg, W, kv)
+    pair.workspace(rows, len(lens), n_dec, 64)
+    pair.step(batch)
