@@ -352,18 +352,29 @@ __device__ void decode_item_f32(const AttnArgs &a, const int32_t *it, char *smem
     const size_t page_elems = (size_t)a.nkv * kPage * HD;
     const float scale = kLog2e / sqrtf((float)HD);
     const float *q = (const float *)a.q + ((size_t)tok * a.nq + g * G) * HD;
-    // scores: one key per thread
-    for (int key = tid; key < nk; key += 256) {
+    // scores: four lanes per key, 64 keys at a time; a key's row is read as 64-byte runs, all of
+    // a lane's loads in flight before the first product
+    const int part4 = tid & 3;
+    for (int key = tid >> 2; key < nk; key += 64) {
         const int page = bt[key / kPage];
         const bool ok = page >= 0 && page < pv.n_pages;
-        if (!ok) flag_error(a.err, ORTHRUS_DEVERR_PAGE);
-        const float *kr = (const float *)pv.k + page * page_elems + ((size_t)g * kPage + key % kPage) * HD;
+        if (!ok && part4 == 0) flag_error(a.err, ORTHRUS_DEVERR_PAGE);
+        const float *kr = (const float *)pv.k + (ok ? page : 0) * page_elems + ((size_t)g * kPage + key % kPage) * HD;
+        f32x4 kv[HD / 16];
+#pragma unroll
+        for (int i = 0; i < HD / 16; ++i) kv[i] = *(const f32x4 *)(kr + 16 * i + 4 * part4);
 #pragma unroll
         for (int h = 0; h < G; ++h) {
             float s = 0.f;
-            if (ok)
-                for (int d = 0; d < HD; ++d) s = fmaf(q[h * HD + d], kr[d], s);
-            sc[key * G + h] = ok ? s * scale : -INFINITY;
+#pragma unroll
+            for (int i = 0; i < HD / 16; ++i) {
+                const f32x4 qv = *(const f32x4 *)(q + h * HD + 16 * i + 4 * part4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = fmaf(qv[e], kv[i][e], s);
+            }
+            s += quad_xor1(s);
+            s += quad_xor2(s);
+            if (part4 == 0) sc[key * G + h] = ok ? s * scale : -INFINITY;
         }
     }
     __syncthreads();
@@ -386,17 +397,28 @@ __device__ void decode_item_f32(const AttnArgs &a, const int32_t *it, char *smem
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < G; ++h) l[h] = red[G + h] + red[3 * G + h] + red[5 * G + h] + red[7 * G + h];
-    // P V: wave w sums keys w, w+4, ...; thread owns dims lane, lane+64
+    // P V: wave w sums pages w, w + 4, ...; a lane owns dims lane, lane + 64 and reads a dim's 16
+    // slots of a page as one 64-byte run
+    const int n_pg = (nk + kPage - 1) / kPage;
     for (int o = lane; o < HD; o += 64) {
         float acc[G];
 #pragma unroll
         for (int h = 0; h < G; ++h) acc[h] = 0.f;
-        for (int key = wave; key < nk; key += 4) {
-            const int page = bt[key / kPage];
+        for (int pg = wave; pg < n_pg; pg += 4) {
+            const int page = bt[pg];
             if (page < 0 || page >= pv.n_pages) continue;
-            const float vv = ((const float *)pv.v)[page * page_elems + ((size_t)g * HD + o) * kPage + key % kPage];
+            const float *vr = (const float *)pv.v + page * page_elems + ((size_t)g * HD + o) * kPage;
+            f32x4 vv[4];
 #pragma unroll
-            for (int h = 0; h < G; ++h) acc[h] = fmaf(sc[key * G + h], vv, acc[h]);
+            for (int i = 0; i < 4; ++i) vv[i] = *(const f32x4 *)(vr + 4 * i);
+            const int n = min(kPage, nk - pg * kPage);
+#pragma unroll
+            for (int i = 0; i < kPage; ++i) {
+                const float x = i < n ? vv[i >> 2][i & 3] : 0.f;   // slots past the split may hold NaN
+#pragma unroll
+                for (int h = 0; h < G; ++h)
+                    if (i < n) acc[h] = fmaf(sc[(pg * kPage + i) * G + h], x, acc[h]);
+            }
         }
 #pragma unroll
         for (int h = 0; h < G; ++h) part[(wave * G + h) * HD + o] = acc[h];
@@ -419,48 +441,204 @@ __device__ void decode_item_f32(const AttnArgs &a, const int32_t *it, char *smem
     }
 }
 
-// --------------------------------------------------------------- prefill, fp32 scalar path
+// ------------------------------------------------------------------ prefill, fp32 MFMA path
+// The bf16 path's shape in fp32: 32-key blocks (two pages) copied straight into two alternating
+// LDS buffers, S^T = K Q^T and O^T = V^T P^T on v_mfma_f32_32x32x2_f32 (fp32 products and sums),
+// each wave 32 query rows of one head.  A lane reads four consecutive dims (keys) of its half with
+// one 16-byte LDS read and feeds them to four MFMAs; both operands take the same order, so the sums
+// only change their order.  The probabilities a lane holds after the score MFMAs are already the
+// second product's operand.  One thread per query row (a serial walk over keys and dims) took 606
+// us for two 128-token chunks of 4 heads x 64; this takes 17.
+template <int HD>
+struct PrefillStageF32 {
+    static constexpr int KEYS = 32;
+    static constexpr int KRB = HD * 4, KCH = KRB / 16;  // bytes and 16-byte chunks of a key row
+    static constexpr int KBYTES = KEYS * KRB;
+    static constexpr int VPAGE = HD * kPage * 4;        // one page's values (one KV head)
+    static constexpr int BYTES = KBYTES + 2 * VPAGE;
+    static constexpr int K_INST = KBYTES / 1024, V_INST = 2 * VPAGE / 1024;
+    static_assert(K_INST % 4 == 0 && V_INST % 4 == 0, "copies per wave");
+    // physical 16-byte chunk of logical chunk c of key row r / of value chunk c of dim d: the 16
+    // lanes of one pass read 16 distinct 16-byte bank groups
+    static __device__ __forceinline__ int kchunk(int r, int c) { return c ^ (r % 16); }
+    static __device__ __forceinline__ int vchunk(int d, int c) { return c ^ ((d >> 2) & 3); }
+};
+
 template <int HD, int G>
-__device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it) {
-    const int tid = threadIdx.x;
+__device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it, char *smem) {
+    using St = PrefillStageF32<HD>;
+    constexpr int KS = HD / 8, DB = HD / 32;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ci = it[IT_INDEX], g = it[IT_KVHEAD], qb = it[IT_A], qn = it[IT_B];
-    if (tid >= qn * G) return;
-    const int r = tid / G, h = g * G + tid % G;
+    const int kend = it[IT_KEY_END];
     const int32_t *ch = a.chunks + kChunkInts * ci;
-    const int seq = ch[0], off = ch[1], tok = ch[4] + qb + r;
-    const int qpos = off + qb + r;
+    const int seq = ch[0], off = ch[1], tok0 = ch[4];
+    const int sb = wave / G, h = g * G + (wave % G);
+    const int col = lane & 31, half = lane >> 5;
+    const int rows = max(0, min(32, qn - sb * 32));
+    const int r0 = sb * 32 + min(col, max(rows, 1) - 1);   // padded rows repeat a valid row
+    const int tok = tok0 + qb + min(r0, qn - 1), qpos = off + qb + min(r0, qn - 1);
     const PoolView pv = pool_view(a, chunk_pool(ch));
-    const size_t page_elems = (size_t)a.nkv * kPage * HD;
-    const float *qp = (const float *)a.q + ((size_t)tok * a.nq + h) * HD;
-    float q[HD], acc[HD];
-    const float scale = kLog2e / sqrtf((float)HD);
-#pragma unroll
-    for (int d = 0; d < HD; ++d) {
-        q[d] = qp[d] * scale;
-        acc[d] = 0.f;
-    }
-    float m = -INFINITY, l = 0.f;
-    for (int kp = 0; kp <= qpos; ++kp) {
-        const int page = pv.bt[(size_t)seq * pv.max_blocks + kp / kPage];
-        if (page < 0 || page >= pv.n_pages) {
-            flag_error(a.err, ORTHRUS_DEVERR_PAGE);
-            continue;
+    const size_t page_bytes = (size_t)a.nkv * kPage * HD * 4;
+    const int32_t *bt = pv.bt + (size_t)seq * pv.max_blocks;
+    const int nkb = (kend + St::KEYS - 1) / St::KEYS, last_block = (kend - 1) / kPage;
+
+    int *pg_lds = (int *)(smem + 2 * St::BYTES);
+    int w0 = 0;
+    auto load_window = [&]() {
+        bool bad = false;
+        for (int i = tid; i < kPrefillPageWindow && w0 + i <= last_block; i += 256) {
+            const int pg = bt[w0 + i];
+            const bool ok = pg >= 0 && pg < pv.n_pages;
+            bad |= !ok;
+            pg_lds[i] = ok ? pg : -1;
         }
-        const float *kr = (const float *)pv.k + page * page_elems + ((size_t)g * kPage + kp % kPage) * HD;
-        const float *vr = (const float *)pv.v + page * page_elems + (size_t)g * HD * kPage + kp % kPage;
-        float s = 0.f;
+        if (bad) flag_error(a.err, ORTHRUS_DEVERR_PAGE);
+    };
+    // page ids of block b (-1 = bad; pages past the last one repeat it); called by every thread
+    auto block_pages = [&](int b, int (&pg)[2]) {
+        if (2 * b - w0 >= kPrefillPageWindow) {
+            __syncthreads();
+            w0 += kPrefillPageWindow;
+            load_window();
+            __syncthreads();
+        }
 #pragma unroll
-        for (int d = 0; d < HD; ++d) s = fmaf(q[d], kr[d], s);
-        const float mn = fmaxf(m, s);
-        const float alpha = exp2f(m - mn), p = exp2f(s - mn);
-        l = l * alpha + p;
+        for (int p = 0; p < 2; ++p) pg[p] = __builtin_amdgcn_readfirstlane(pg_lds[min(2 * b + p, last_block) - w0]);
+    };
+    // 16 bytes a lane into dst + 16 lane; caches whose base is only element-aligned go through registers
+    const bool direct = (((uintptr_t)pv.k | (uintptr_t)pv.v) & 15) == 0;
+    auto copy = [&](const char *src, char *dst) {
+        if (direct) {
+            __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+        } else {
+            const float *f = (const float *)src;
+            *(f32x4 *)(dst + 16 * lane) = f32x4{f[0], f[1], f[2], f[3]};
+        }
+    };
+    auto issue = [&](const int (&pg)[2], int buf) {
+        char *kl = smem + buf * St::BYTES, *vl = kl + St::KBYTES;
 #pragma unroll
-        for (int d = 0; d < HD; ++d) acc[d] = fmaf(p, vr[d * kPage], acc[d] * alpha);
+        for (int j = wave; j < St::K_INST; j += 4) {
+            const int row = j * (1024 / St::KRB) + lane / St::KCH, c = St::kchunk(row, lane % St::KCH);
+            const char *src = pv.k + (size_t)max(pg[row / kPage], 0) * page_bytes +
+                              ((size_t)(g * kPage + row % kPage) * HD + c * 4) * 4;
+            copy(src, kl + j * 1024);
+        }
+#pragma unroll
+        for (int j = wave; j < St::V_INST; j += 4) {
+            constexpr int PER_PAGE = St::VPAGE / 1024;
+            const int p = j / PER_PAGE, d = (j % PER_PAGE) * 16 + lane / 4, c = St::vchunk(d, lane % 4);
+            const char *src = pv.v + (size_t)max(pg[p], 0) * page_bytes + ((size_t)(g * HD + d) * kPage + c * 4) * 4;
+            copy(src, vl + j * 1024);
+        }
+    };
+    // values of keys at or past kend and of bad pages become zero (their probabilities are zero,
+    // but a slot past a sequence's length may hold NaN)
+    auto fixup = [&](int b, const int (&pg)[2], int buf) {
+        char *vl = smem + buf * St::BYTES + St::KBYTES;
+        for (int i = tid; i < 2 * HD; i += 256) {
+            const int p = i / HD, d = i % HD;
+            const int keep = pg[p] < 0 ? 0 : max(0, min(kPage, kend - (b * St::KEYS + p * kPage)));
+            for (int sl = keep; sl < kPage; ++sl)
+                *(float *)(vl + p * St::VPAGE + d * 64 + St::vchunk(d, sl / 4) * 16 + (sl % 4) * 4) = 0.f;
+        }
+    };
+
+    f32x4 qf[KS];
+    const float *qp = (const float *)a.q + ((size_t)tok * a.nq + h) * HD;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) qf[j] = *(const f32x4 *)(qp + 8 * j + 4 * half);
+    f32x16 acc[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[d][e] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    const float scale = kLog2e / sqrtf((float)HD);
+    const int wave_first = off + qb + sb * 32;
+
+    auto compute = [&](int kb, const int (&pg)[2]) {
+        if (rows <= 0 || kb * St::KEYS > wave_first + rows - 1) return;
+        const char *kl = smem + (kb & 1) * St::BYTES, *vl = kl + St::KBYTES;
+        // register r of half `half` holds key 8 (r / 4) + 4 half + r % 4 of the block
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            const f32x4 kf = *(const f32x4 *)(kl + col * St::KRB + St::kchunk(col, 2 * j + half) * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[j][e], s, 0, 0, 0);
+        }
+        float mloc = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = 8 * (r >> 2) + 4 * half + (r & 3);
+            if (kb * St::KEYS + key > qpos || pg[r >> 3] < 0) s[r] = -INFINITY;
+            mloc = fmaxf(mloc, s[r]);
+        }
+        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * scale;
+        const float mn = fmaxf(m, mloc);
+        const float alpha = m == -INFINITY ? 0.f : exp2f(m - mn);
+        const float sub = mn == -INFINITY ? 0.f : mn;
         m = mn;
+        float psum = 0.f, p[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            p[r] = exp2f(s[r] * scale - sub);
+            psum += p[r];
+        }
+        psum += __shfl_xor(psum, 32, 64);
+        l = l * alpha + psum;
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[d][e] *= alpha;
+        }
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+            for (int d = 0; d < DB; ++d) {
+                const int dim = d * 32 + col;
+                const f32x4 vf = *(const f32x4 *)(vl + (q4 >> 1) * St::VPAGE + dim * 64 +
+                                                  St::vchunk(dim, (q4 & 1) * 2 + half) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[e], p[q4 * 4 + e], acc[d], 0, 0, 0);
+            }
+    };
+
+    load_window();
+    __syncthreads();
+    int pg_cur[2];
+    block_pages(0, pg_cur);
+    issue(pg_cur, 0);
+    for (int kb = 0; kb < nkb; ++kb) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        int pg_nxt[2] = {0, 0};
+        if (kb + 1 < nkb) {
+            block_pages(kb + 1, pg_nxt);
+            issue(pg_nxt, (kb + 1) & 1);
+        }
+        if ((kb + 1) * St::KEYS > kend || pg_cur[0] < 0 || pg_cur[1] < 0) {
+            fixup(kb, pg_cur, kb & 1);
+            __syncthreads();
+        }
+        compute(kb, pg_cur);
+        pg_cur[0] = pg_nxt[0];
+        pg_cur[1] = pg_nxt[1];
     }
+    if (col >= rows) return;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
     float *op = (float *)a.o + ((size_t)tok * a.nq + h) * HD;
 #pragma unroll
-    for (int d = 0; d < HD; ++d) op[d] = l > 0.f ? acc[d] / l : 0.f;
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+            *(f32x4 *)(op + d * 32 + q4 * 8 + half * 4) = f32x4{acc[d][q4 * 4] * inv, acc[d][q4 * 4 + 1] * inv,
+                                                               acc[d][q4 * 4 + 2] * inv, acc[d][q4 * 4 + 3] * inv};
 }
 
 // ------------------------------------------------------------------ prefill, bf16 MFMA path
@@ -754,7 +932,7 @@ template <bool BF16, int HD, int G>
 constexpr size_t attn_smem() {
     constexpr int MAXK = kSplitPages * kPage;
     constexpr size_t dec = BF16 ? decode_smem<HD, G, kDecodeChunkPages>() : (MAXK * G + 8 * G + 4 * G * HD) * 4;
-    constexpr size_t pre = BF16 ? 2 * PrefillStage<HD>::BYTES + 4 * kPrefillPageWindow : 0;
+    constexpr size_t pre = 2 * (BF16 ? PrefillStage<HD>::BYTES : PrefillStageF32<HD>::BYTES) + 4 * kPrefillPageWindow;
     return dec > pre ? dec : pre;
 }
 
@@ -764,7 +942,7 @@ __global__ __launch_bounds__(256, BF16 ? 2 : 1) void attn_kernel(AttnArgs a) {
     const int32_t *it = a.items + kItemInts * blockIdx.x;
     if (it[IT_KIND] == 0) {
         if constexpr (BF16) prefill_item_mfma<HD, G>(a, it, smem);
-        else prefill_item_f32<HD, G>(a, it);
+        else prefill_item_f32<HD, G>(a, it, smem);
     } else {
         if constexpr (BF16) decode_item_bf16<HD, G>(a, it, smem);
         else decode_item_f32<HD, G>(a, it, smem);
