@@ -56,22 +56,7 @@ __device__ __forceinline__ void flag_error(int *err, int bit) { atomicOr(err, bi
 // ---------------------------------------------------------------------------------------
 // launchers (host functions defined next to their kernels)
 // ---------------------------------------------------------------------------------------
-enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2, EPI_QKV_ROPE = 3 };
-
-// QKV projection epilogue (bf16 path): rotate q and k at each token's position, store q for
-// attention and append rotated k and raw v to the paged cache (Section 3.2's cache writes)
-struct QkvRope {
-    const float2 *cs;          // [T][hd/2] (cos, sin) of each token's position
-    const int32_t *pos, *seq;  // per token (global token index)
-    void *q_out;               // [T][nq][hd]
-    void *k_cache[2], *v_cache[2];          // layer base per pool
-    const int32_t *block_table[2];
-    int n_pages[2], max_blocks[2];
-    int row0;                  // global token index of the launch's row 0
-    int Te;                    // tokens < Te use pool 0, others pool 1
-    int nq, nkv, hd, page;
-    int *err;
-};
+enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_ADD_F32 = 1, EPI_SWIGLU = 2 };
 
 // LoRA update of a projection (rows [0, rows) of the launch): out += U B^T, with U [rows][ldu]
 // the scaled, per-row-masked shrink x A^T of the n adapters in use side by side (adapter j owns
@@ -95,7 +80,6 @@ struct GemmArgs {
     int splits;
     float *partial;
     size_t split_stride;
-    QkvRope rope;    // EPI_QKV_ROPE only
     LoraGemm lora;   // adds the low-rank update before the epilogue (split 0 of a split-K launch)
     // B0 in the 64 x 64 blocked layout ([ceil(N/64)][K/64][64][64]; bf16 path, not SwiGLU):
     // one tile stage reads whole 8 KB runs instead of 128-byte pieces of 64 rows
@@ -113,6 +97,8 @@ hipError_t launch_block_weights(const void *src, void *dst, int rows, int cols, 
 // evenly as the count allows) for a bf16 residual-add projection of this shape; launch_gemm
 // ignores a requested split count larger than K's number of stages
 int gemm_add_splits(int M, int N, int K, int max_splits, bool wide);
+// the same for a QKV projection (1 or 2), whose rows or partial sums launch_rope_append reads
+int gemm_qkv_splits(int M, int N, int K, bool wide);
 
 // LoRA shrink: u[row][j*r + k] = scale[j] * sum_i x[row][i] a_j[k][i] for the adapter j of the
 // row (row_adapter[row]), 0 in the other adapters' columns.  x [rows][K] with row stride ldx,

@@ -50,10 +50,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_bf16_kernel(GemmArgs a) 
     static_assert(A_INST * RPI * NW == BM && B_INST * RPI * NW == BN, "copy split");
     static_assert(FM >= 1 && FN >= 1 && (EPI != EPI_SWIGLU || FN % 2 == 0), "tile shape");
     static_assert(SD >= 2 && IN_FLIGHT < 64, "pipeline depth");
-    // the QKV epilogue stages the fp32 tile (rows padded to 136 floats) and per-row metadata
-    constexpr int CROW = 136;
-    constexpr int EPI_BYTES = EPI == EPI_QKV_ROPE ? BM * CROW * 4 + BM * 16 : 0;
-    __shared__ __attribute__((aligned(1024))) char smem[RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES];
+    __shared__ __attribute__((aligned(1024))) char smem[RING_BYTES];
     char *const smem_b = smem + STAGES * BM * ROWB;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -257,104 +254,6 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_bf16_kernel(GemmArgs a) 
         }
     }
 
-    if constexpr (EPI == EPI_QKV_ROPE) {
-        // Rotation of q and k at each token's position (pairs (i, i + hd/2)), q stored for
-        // attention, rotated k and raw v appended to the paged cache.  The fp32 tile goes
-        // through LDS so every store is a 16-byte piece: 8 dims of a q or k row, or (values,
-        // dim-major pages) 8 consecutive slots of one dim when 8 rows fill them.
-        static_assert(BN == 128, "tiles of whole heads");
-        const QkvRope &q = a.rope;
-        float *ct = (float *)smem;                       // [BM][CROW] fp32 tile
-        int4 *meta = (int4 *)(smem + BM * CROW * 4);     // per row {token, slot, page or -1, pool}
-        __syncthreads();                                 // every wave is done with the stage buffers
-#pragma unroll
-        for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < FN; ++ni)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = wm * TM + mi * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                    ct[row * CROW + wn * TN + ni * 32 + (lane & 31)] = acc[mi][ni][r];
-                }
-        for (int rr = tid; rr < BM; rr += 64 * NW) {
-            const int lr = m0 + rr;
-            int4 md{-1, 0, -1, 0};
-            if (lr < a.M) {
-                const int t = q.row0 + lr;
-                const int pos = q.pos[t], sq = q.seq[t], pl = t < q.Te ? 0 : 1;
-                const int page = q.block_table[pl][(size_t)sq * q.max_blocks[pl] + pos / q.page];
-                const bool ok = page >= 0 && page < q.n_pages[pl];
-                // flagged once per row: by the tile holding the first key head
-                if (!ok && n0 == q.nq * q.hd) flag_error(q.err, ORTHRUS_DEVERR_PAGE);
-                md = int4{t, pos % q.page, ok ? page : -1, pl};
-            }
-            meta[rr] = md;
-        }
-        __syncthreads();
-        const int hd = q.hd, half = hd / 2, G8 = half / 8;
-        for (int h2 = 0; h2 < 128 / hd; ++h2) {
-            const int head = (n0 + h2 * hd) / hd;
-            if (head < q.nq + q.nkv) {
-                // q or k: items (row, group of 8 pairs)
-                const bool is_q = head < q.nq;
-                const int kvh = head - q.nq;
-                for (int it = tid; it < BM * G8; it += 64 * NW) {
-                    const int row = it / G8, g = it % G8;
-                    const int4 md = meta[row];
-                    if (md.x < 0 || (!is_q && md.z < 0)) continue;
-                    const float *lo = ct + row * CROW + h2 * hd + g * 8, *hi = lo + half;
-                    const float4 *csp = (const float4 *)(q.cs + (size_t)md.x * half + g * 8);
-                    u32x4 w1, w2;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float4 cs = csp[e];   // (cos, sin) of pairs 2e and 2e + 1
-                        const float a0 = lo[2 * e], a1 = lo[2 * e + 1], b0 = hi[2 * e], b1 = hi[2 * e + 1];
-                        w1[e] = pack_bf16x2(a0 * cs.x - b0 * cs.y, a1 * cs.z - b1 * cs.w);
-                        w2[e] = pack_bf16x2(b0 * cs.x + a0 * cs.y, b1 * cs.z + a1 * cs.w);
-                    }
-                    bf16 *dst = is_q ? (bf16 *)q.q_out + ((size_t)md.x * q.nq + head) * hd
-                                     : (bf16 *)q.k_cache[md.w] + (((size_t)md.z * q.nkv + kvh) * q.page + md.y) * hd;
-                    *(u32x4 *)(dst + g * 8) = w1;
-                    *(u32x4 *)(dst + half + g * 8) = w2;
-                }
-            } else {
-                // v: items (dim, group of 8 rows); a dim of one page holds `page` slots contiguously.
-                // Adjacent lanes take the two 8-row halves of one dim's 16 rows, so a page-aligned
-                // run of 16 rows leaves as whole 32-byte runs of consecutive dims (7B-layer mixed
-                // step: 80.3 -> 78.8 us against lanes along the dims)
-                static_assert(BM % 16 == 0, "16-row groups");
-                const int kvh = head - q.nq - q.nkv;
-                for (int it = tid; it < hd * (BM / 8); it += 64 * NW) {
-                    const int d = (it >> 1) % hd, r0 = ((it >> 1) / hd) * 16 + (it & 1) * 8;
-                    const int4 m0d = meta[r0];
-                    bool run = m0d.x >= 0 && m0d.z >= 0 && (m0d.y & 7) == 0;
-#pragma unroll
-                    for (int k = 1; k < 8; ++k) {
-                        const int4 mk = meta[r0 + k];
-                        run = run && mk.z == m0d.z && mk.w == m0d.w && mk.y == m0d.y + k;
-                    }
-                    const float *col = ct + r0 * CROW + h2 * hd + d;
-                    if (run) {
-                        u32x4 w;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(col[(2 * e) * CROW], col[(2 * e + 1) * CROW]);
-                        bf16 *vc = (bf16 *)q.v_cache[m0d.w] + (((size_t)m0d.z * q.nkv + kvh) * hd + d) * q.page + m0d.y;
-                        *(u32x4 *)vc = w;
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const int4 mk = meta[r0 + k];
-                            if (mk.x < 0 || mk.z < 0) continue;
-                            bf16 *vc = (bf16 *)q.v_cache[mk.w] + (((size_t)mk.z * q.nkv + kvh) * hd + d) * q.page + mk.y;
-                            *vc = (bf16)col[k * CROW];
-                        }
-                    }
-                }
-            }
-        }
-        return;
-    }
-
     if constexpr (EPI == EPI_SWIGLU) {
         // The MFMA layout leaves each lane one column of 16 rows per fragment, i.e. 2-byte
         // stores per output.  Instead the BM x BN/2 bf16 output tile is staged through the
@@ -529,56 +428,54 @@ hipError_t run_bf16(const GemmArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile choice per shape, from measurements of the step's projections on MI355X (M = 1088
-// tokens of a 7B-class layer).  Copy latency, not LDS or MFMA issue, bounds these GEMMs, so
-// the choice trades tile reuse against filling the CUs:
+// One 256-row tile per 128 weight rows, the weights streamed once (256x128 tiles of this file): its
+// estimated length, measured 1.06 us per K stage and round of 256 workgroups (7B gate/up of 256
+// rows 73.8 us), against plan_big's estimate of the same launch.
+double stream256_us(int weight_rows, int K) {
+    return ((weight_rows + 127) / 128 + 255) / 256 * (K / BK * 1.06 + 6.0);
+}
+
+// Split-K projections of 129..256 rows whose 128x128 tiles fill most of the chip with long K runs
+// stay on this file's 4-deep rings (7B down, 4 splits: 160 rows 41.9 us against 48.2 on the best
+// shape of gemm_big.hip, 256 rows 46.7 against 50.4); shorter runs or fewer workgroups are faster
+// there (o 16.2 against 13.7 us, 2048-wide down 22.9 against 17.9 us).
+bool ring_split(int M, int N, int K, int splits) {
+    const long blocks = (long)((M + 127) / 128) * ((N + 127) / 128) * splits;
+    return M > 128 && M <= 256 && blocks >= 192 && K / splits >= 2048;
+}
+
+// Tile choice per shape, from measurements of the step's projections on MI355X (7B-class layer, cold
+// weights unless said otherwise):
 //  - M <= 64 (decode-only batches, the LM head): weight streaming; 64x64 tiles (more
 //    workgroups) with a 4-deep copy ring keep enough bytes in flight per CU (LM head
 //    64 x 32000 x 4096: 70 -> 43 us with warm caches; decode-batch QKV 35 -> 25 us); gate/up
-//    on 64x128 tiles (224 workgroups instead of 112: 58.6 -> 43.9 us with cold weights);
-//  - every projection above 896 rows that has the chip to itself: the kernel of gemm_big.hip;
-//    beside another stream's launches (GemmArgs::wide) it leaves no registers and no LDS for that
-//    stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against 5.99 ms), and
-//    the kernel of this file stays;
-//  - gate/up above 896 rows (wide): 192x256 or 256x256 tiles over 8 waves, whichever needs fewer
-//    rounds of workgroups times tile rows;
-//  - gate/up of 129..256 rows: one 256x128 row tile, the weights streamed once (non-temporal)
-//    through 3-deep rings (M = 256 with cold weights: 110 -> 71 us against 128x128 tiles);
-//  - residual-add projections of M > 896 rows (wide): 256x256 tiles over 8 waves with the
-//    split-K count gemm_add_splits picks (o 58 -> 46 us, down 177 -> 135 us against 128x128
-//    tiles at M = 1088);
-//  - otherwise 128x128 (64 KiB of LDS, two workgroups per CU hide each other's waits).
-//  - medium M (64 < M <= 896: decode-heavy and small mixed batches, where the weights stream):
-//    more, smaller workgroups and deeper split-K for the residual-add projections (down at
-//    M = 384: 124 -> 57 us; o: 42 -> 23 us), 64x128 tiles for QKV up to M = 512, and for
-//    gate/up up to M = 896 the 128- or 192-row tile that pads M least (M = 512: 162 -> 129 us);
+//    on 64x128 tiles (224 workgroups instead of 112: 58.6 -> 43.9 us);
 //  - 64 < M <= 128 (decode batches of up to 128 rows): one row tile of 128 rows and a 4-deep
 //    ring (128 KiB of LDS), weights streamed: gate/up 66.5 -> 47.3 us, LM head 74.6 -> 66.5 us,
-//    down split 4 ways on 128x64 tiles 38.8 -> 32.7 us (M = 96, cold weights);
-//  - split-K residual-add projections of 128 < M <= 256: 128x128 tiles with 4-deep rings (one
-//    workgroup per CU; down at M = 192 57.1 -> 45.7 us, o at M = 256 27.1 -> 21.8 us); above 256
-//    rows two 64 KiB workgroups per CU win again (down at M = 384: 71 against 86 us).  Run
-//    concurrently with another stream (GemmArgs::wide), the same projections take 256x256
-//    tiles: 4x fewer workgroup-microseconds per flop at a longer launch, which the other
-//    stream's launches fill (the two-model 32-layer step, QKV, o and down of the generator's
-//    256 decode rows so tiled: 23.4 -> 22.5 ms and 23.9 -> 23.2 ms on two GPUs; the
-//    generator's gate/up on such tiles as well measured slower);
-//  - gate/up of 256 < M <= 896, measured on the 7B shape with cold weights: 192x256 when
-//    128x128 tiles need more than the 512 slots of one round and 192x256 tiles fit in one
-//    (M = 640: 172 against 195 us), else the tile that pads M least (M = 384 98 against 130 us,
-//    M = 512 147 against 174 us, M = 896 240 against 256 us).
+//    down split 4 ways on 128x64 tiles 38.8 -> 32.7 us (M = 96);
+//  - 128 < M <= 256: gate/up and stored rows on one 256x128 row tile with the weights streamed once
+//    (non-temporal) where that is the shorter estimate, long split-K runs as ring_split says;
+//  - everything else above 128 rows that has the chip to itself: gemm_big.hip (370 / 544 / 896
+//    rows: gate/up 93.5 / 169.7 / 246.9 -> 84.6 / 129.8 / 190.3 us, down 68.4 / 116.1 / 124.3 ->
+//    56.8 / 74.4 / 87.8, o 22.9 / 35.1 / 37.8 -> 18.9 / 25.4 / 33.0; 2048-wide layer, 370 rows:
+//    42.5, 26.7, 12.3 -> 31.6, 22.0, 10.3);
+//  - beside another stream's launches (GemmArgs::wide) the large kernel leaves no registers and no
+//    LDS for that stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against
+//    5.99 ms), and this file's tiles stay: split-K projections of 129..256 rows and of more than
+//    896 on 256x256 (fewest workgroup-microseconds per flop; the other stream's launches fill the
+//    rest), gate/up above 256 rows on the 192x256, 256x256 or 128x128 tiles that need the fewest
+//    rounds or pad the rows least.
 template <int EPI>
 hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
     const bool big = !a.wide && gemm_big_takes(a);
-    if constexpr (EPI == EPI_QKV_ROPE) {
-        if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
-        if (a.M <= 512) return run_bf16<64, 128, 1, 4, EPI, 64, 3>(a, s);
-        return run_bf16<128, 128, 2, 2, EPI>(a, s);
-    } else if constexpr (EPI == EPI_SWIGLU) {
+    if constexpr (EPI == EPI_SWIGLU) {
         if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
+        if (big) {
+            const BigPlan p = plan_big(a.M, a.N, a.K, true, 1);
+            if (a.M > 256 || p.us < stream256_us(2 * a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
+        }
         if (a.M <= 256) return run_bf16<256, 128, 4, 2, EPI, 64, 3, 3, true>(a, s);
-        if (big && a.M > 896) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, true, 1), s);
         if (a.M > 896) {
             // the row tile whose rounds of workgroups over 256 CUs cost least, a round costing
             // its tile's rows
@@ -599,18 +496,16 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         const bool split = EPI == EPI_ADD_F32 && a.partial && a.splits > 1;
         if (split && a.M <= 128) return run_bf16<128, 64, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (EPI != EPI_ADD_F32 && a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
+        if (a.M <= 128) return run_bf16<128, 128, 4, 2, EPI>(a, s);
+        if (big && !(split && ring_split(a.M, a.N, a.K, a.splits))) {
+            const BigPlan p = plan_big(a.M, a.N, a.K, false, split ? a.splits : 1);
+            if (a.M > 256 || EPI == EPI_ADD_F32 || p.us < stream256_us(a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
+        }
         // stored rows of 129..256 (the LM head of up to 256 decode rows): one 256-row tile, the
         // weights streamed once
         if (EPI == EPI_STORE_F32 && a.M <= 256) return run_bf16<256, 128, 4, 2, EPI, 64, 3, 3, true>(a, s);
-        if (split && a.wide && a.M > 128 && a.M <= 256) return run_bf16<256, 256, 2, 4, EPI>(a, s);
+        if (a.wide && ((split && a.M <= 256) || a.M > 896)) return run_bf16<256, 256, 2, 4, EPI>(a, s);
         if (split && a.M <= 256) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, false>(a, s);
-        if (split && a.M <= 896) return run_bf16<128, 128, 2, 2, EPI>(a, s);
-        if (big && EPI == EPI_ADD_F32 && a.partial && a.M > 896) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, false, a.splits), s);
-        if (EPI == EPI_ADD_F32 && a.partial && a.M > 896) return run_bf16<256, 256, 2, 4, EPI>(a, s);
-        if (EPI == EPI_ADD_F32) return run_bf16<128, 128, 4, 2, EPI>(a, s);
-        // fp32 rows of a large QKV projection (rotated by a row kernel)
-        if (big && a.M > 1280) return launch_gemm_big(EPI, a, plan_big(a.M, a.N, a.K, false, 1), s);
-        if (a.M > 1280) return run_bf16<256, 256, 2, 4, EPI>(a, s);
         return run_bf16<128, 128, 2, 2, EPI>(a, s);
     }
 }
@@ -622,14 +517,19 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
 // as evenly as the count allows), at least 512 deep.  1 = no split.
 //  - M <= 64 (64x64 tiles): the factor whose workgroups fill the last round over 256 CUs best,
 //    the smaller one on a tie;
-//  - 64 < M <= 896, from measurements of the 7B projections: 4 up to M = 640 (64x64 or 128x128
-//    tiles; weight streaming wants many workgroups), then 2;
-//  - M > 896: the factor whose cover of the output (plan_big) and slabs take least time; beside
-//    another stream's launches (wide) the factor with the least (rounds of workgroups over 256
-//    CUs) x (stages per split), the smaller one on a tie.
+//  - 64 < M <= 128: 4 (weight streaming wants many workgroups);
+//  - M > 128: 4 for the long runs of ring_split, else the factor whose cover of the output
+//    (plan_big) and slabs take least time;
+//  - beside another stream's launches (wide): 4 up to M = 640, then 2 (128x128 tiles), above 896
+//    (256x256 tiles, one workgroup per CU) the factor with the least (rounds of workgroups over
+//    256 CUs) x (stages per split), the smaller one on a tie.
 int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
     auto valid = [&](int s) { return s <= max_splits && K % BK == 0 && K / s >= 512; };
-    if (M > 896 && wide) {
+    if (M > 128 && !wide) {
+        if (valid(4) && ring_split(M, N, K, 4)) return 4;
+        return big_splits(M, N, K, max_splits);
+    }
+    if (M > 896) {
         const int stages = K / BK;
         const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
         int best = 1;
@@ -638,18 +538,6 @@ int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
             if (s > 1 && !valid(s)) continue;
             const long cost = (tiles * s + 255) / 256 * ((stages + s - 1) / s);
             if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
-        }
-        return best;
-    }
-    if (M > 896) {
-        int best = 1;
-        double best_cost = 0.0;
-        for (int s = 1; s <= max_splits; ++s) {
-            if (s > 1 && !valid(s)) continue;
-            // a slab is written here and read by the next row kernel: 8 bytes per value at about
-            // 4 TB/s, in stage times of 1.45 us
-            const double cost = plan_big(M, N, K, false, s).cost + s * ((double)M * N * 8 / 4e6 / 1.45);
-            if (best_cost == 0.0 || cost < best_cost) { best = s; best_cost = cost; }
         }
         return best;
     }
@@ -668,6 +556,16 @@ int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
         if (f > best_fill + 1e-9) { best = s; best_fill = f; }
     }
     return best;
+}
+
+// Splits (1 or 2) of a QKV projection, whose fp32 rows or partial sums the rotation/append kernel
+// reads: two for up to 128 rows (whole-K tiles leave too few workgroups for the weights: 64 rows of
+// the 7B shape 42.6 -> 18.6 us, rotation included 25.5) and beside another stream's launches up to
+// 1280 rows, else as the covers' estimates say.
+int gemm_qkv_splits(int M, int N, int K, bool wide) {
+    if (K % (2 * BK) || K / 2 < 512) return 1;
+    if (M <= 128 || (wide && M <= 1280)) return 2;
+    return wide ? 1 : big_splits(M, N, K, 2);
 }
 
 // dst [ceil(rows/64)][cols/64][64][64] <- src [rows][cols] (bf16), one 16-byte piece per thread
@@ -701,13 +599,9 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
         switch (epi) {
             case EPI_STORE_F32: return dispatch_bf16<EPI_STORE_F32>(a, s);
             case EPI_ADD_F32: return dispatch_bf16<EPI_ADD_F32>(a, s);
-            case EPI_QKV_ROPE:
-                if (a.rope.hd != 64 && a.rope.hd != 128) return hipErrorInvalidValue;
-                return dispatch_bf16<EPI_QKV_ROPE>(a, s);
             default: return dispatch_bf16<EPI_SWIGLU>(a, s);
         }
     }
-    if (epi == EPI_QKV_ROPE) return hipErrorInvalidValue;   // fp32 path: GEMM, then rope_append
     const dim3 grid((a.N + 31) / 32, (a.M + 31) / 32), block(64 * kF32Waves);
     switch (epi) {
         case EPI_STORE_F32: hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE_F32>, grid, block, 0, s, a); break;

@@ -23,8 +23,6 @@
 // (see plan_big).
 #include <algorithm>
 #include <type_traits>
-#include <utility>
-#include <vector>
 
 #include "gemm_common.hpp"
 #include "gemm_big.hpp"
@@ -38,6 +36,7 @@ constexpr int kRowBytes = kBK * 2;
 constexpr int kWaves = 8;
 constexpr int kRingA = 2, kRingB = 3;
 constexpr int kLds = 160 * 1024;
+constexpr int ring_bytes(int bm, int bn) { return (kRingA * bm + kRingB * bn) * kRowBytes; }
 typedef __attribute__((address_space(3))) void lds_void;
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -49,16 +48,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_buffer(const void *p, siz
 
 // One BM x BN tile (BN weight rows; SwiGLU: BN / 2 gate and as many up rows) over K stages
 // [kt0, kt0 + nk).  WM x WN waves.
-template <int BM, int BN, int WM, int WN, int EPI>
+template <int BM, int BN, int WM, int WN, bool SW>
 __device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, int n0, int kt0, int nk, int split,
-                                         int splits) {
+                                         const BigPlan &p) {
     static_assert(WM * WN == kWaves, "eight waves");
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16;
-    constexpr bool SW = EPI == EPI_SWIGLU;
     constexpr int A_INST = BM / (8 * kWaves), B_INST = BN / (8 * kWaves), INST = A_INST + B_INST;
     constexpr int ABUF = BM * kRowBytes, BBUF = BN * kRowBytes, B_BASE = kRingA * ABUF;
     static_assert(A_INST * 8 * kWaves == BM && B_INST * 8 * kWaves == BN, "copies divide over the waves");
-    static_assert(kRingA * ABUF + kRingB * BBUF <= kLds && TM % 16 == 0 && TN % 16 == 0, "tile");
+    static_assert(ring_bytes(BM, BN) <= kLds && TM % 16 == 0 && TN % 16 == 0, "tile");
     static_assert(!SW || (FN % 2 == 0 && TN % 16 == 0), "gate and up halves of a wave");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -239,7 +237,7 @@ __device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, 
     if constexpr (SW) {
         // the bf16 output tile through LDS, so that its rows leave as whole 16-byte pieces
         constexpr int OC = BN / 2, OROW = OC * 2 + 16;
-        static_assert(BM * OROW <= kLds, "output tile");
+        static_assert(BM * OROW <= ring_bytes(BM, BN), "output tile");
         __syncthreads();
 #pragma unroll
         for (int mi = 0; mi < FM; ++mi)
@@ -261,8 +259,8 @@ __device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, 
     }
     // fp32 rows: stored, added into the residual stream, or this split's share into its own slab.
     // 16-byte stores where the rows allow them
-    float *base = splits > 1 ? a.partial + (size_t)split * a.split_stride : (float *)a.out;
-    const bool add = EPI == EPI_ADD_F32 && splits == 1;
+    float *base = p.splits > 1 ? a.partial + (size_t)split * a.split_stride : (float *)a.out;
+    const bool add = p.add && p.splits == 1;
     const bool vec = a.ldo % 4 == 0 && (uintptr_t)base % 16 == 0;
 #pragma unroll
     for (int mi = 0; mi < FM; ++mi) {
@@ -295,25 +293,28 @@ __device__ __forceinline__ int xcd_run(int b, int n) {
 
 // Blocks [0, main * splits): 256 x 256 tiles over row tiles [0, m_main) and the first n_main column
 // tiles; the rest: tiles of the second shape over the remaining columns (of every row) or rows.
-template <int EPI, int BM2, int BN2, int WM2, int WN2>
+// MAIN false: the second shape covers everything (and the workgroup takes only its LDS).
+template <bool SW, bool MAIN, int BM2, int BN2, int WM2, int WN2>
 __global__ __launch_bounds__(64 * kWaves, 1) void gemm_big_kernel(GemmArgs a, BigPlan p) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ __attribute__((aligned(1024))) char smem[kLds];
-    constexpr int C1 = EPI == EPI_SWIGLU ? 128 : 256, C2 = EPI == EPI_SWIGLU ? BN2 / 2 : BN2;
-    const int n1 = p.m_main * p.n_main, n2 = p.m_alt * p.n_alt, stages = a.K / kBK;
+    __shared__ __attribute__((aligned(1024))) char smem[MAIN ? kLds : ring_bytes(BM2, BN2)];
+    constexpr int C1 = SW ? 128 : 256, C2 = SW ? BN2 / 2 : BN2;
+    const int n1 = MAIN ? p.m_main * p.n_main : 0, n2 = p.m_alt * p.n_alt, stages = a.K / kBK;
     int b = blockIdx.x;
-    if (b < n1 * p.splits) {
-        const int split = b / n1, t = xcd_run(b % n1, n1);
-        const int kt0 = (int)((long)split * stages / p.splits), kt1 = (int)((long)(split + 1) * stages / p.splits);
-        big_tile<256, 256, 4, 2, EPI>(a, smem, t % p.m_main * 256, t / p.m_main * C1, kt0, kt1 - kt0, split, p.splits);
-        return;
+    if constexpr (MAIN) {
+        if (b < n1 * p.splits) {
+            const int split = b / n1, t = xcd_run(b % n1, n1);
+            const int kt0 = (int)((long)split * stages / p.splits), kt1 = (int)((long)(split + 1) * stages / p.splits);
+            big_tile<256, 256, 4, 2, SW>(a, smem, t % p.m_main * 256, t / p.m_main * C1, kt0, kt1 - kt0, split, p);
+            return;
+        }
     }
     if constexpr (BM2 > 0) {
         b -= n1 * p.splits;
         const int split = b / n2, t = xcd_run(b % n2, n2);
         const int kt0 = (int)((long)split * stages / p.splits), kt1 = (int)((long)(split + 1) * stages / p.splits);
-        big_tile<BM2, BN2, WM2, WN2, EPI>(a, smem, p.row_alt + t % p.m_alt * BM2, p.col_alt + t / p.m_alt * C2, kt0, kt1 - kt0,
-                                          split, p.splits);
+        big_tile<BM2, BN2, WM2, WN2, SW>(a, smem, p.row_alt + t % p.m_alt * BM2, p.col_alt + t / p.m_alt * C2, kt0, kt1 - kt0,
+                                         split, p);
     }
 #endif
 }
@@ -321,58 +322,75 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_big_kernel(GemmArgs a, Bi
 // time of the last of n1 tiles of cost c1, then n2 of cost c2, handed in order to 256 CUs as
 // they become free
 double makespan(long n1, double c1, long n2, double c2) {
-    std::vector<std::pair<double, long>> busy{{0.0, 256}};   // (free at, CUs), ascending
-    double last = 0.0;
-    auto deal = [&](long n, double c) {
-        while (n > 0) {
-            const auto [t, k] = busy.front();
-            const long take = std::min(n, k);
-            if (take == k) busy.erase(busy.begin());
-            else busy.front().second -= take;
-            const std::pair<double, long> done{t + c, take};
-            busy.insert(std::upper_bound(busy.begin(), busy.end(), done), done);
-            last = std::max(last, t + c);
-            n -= take;
+    const long r = n1 / 256, k = n1 % 256;
+    const double ta = r * c1, tb = ta + c1;          // 256 - k CUs are free at ta, k at tb
+    double end = k ? tb : ta;
+    if (n2 == 0) return end;
+    // the least time by which the CUs finish n2 more tiles: a tile's end on one of the two groups
+    double best = -1.0;
+    for (long i = 0; best < 0.0; ++i) {
+        const double at[2] = {ta + i * c2, tb + i * c2};
+        for (const double t : at) {
+            if (k == 0 && t != at[0]) continue;
+            const long done = (long)((t - ta) / c2 + 1e-9) * (256 - k) + (t > tb ? (long)((t - tb) / c2 + 1e-9) * k : 0);
+            if (done >= n2 && (best < 0.0 || t < best)) best = t;
         }
-    };
-    deal(n1, c1);
-    deal(n2, c2);
-    return last;
+    }
+    return std::max(end, best);
 }
+
+// Microseconds of a K stage of a bm x bn tile, and of the rest of a tile (prologue, epilogue).
+// Measured over the 7B and the 2048-wide shapes at 160..2048 rows: 256x256 1.45, 256x192 and
+// 192x256 1.15-1.18, 192x192 1.0, 128x256 0.95-0.97, 192x128 0.82-0.87, two 128x128 side by side
+// on one CU 0.93.
+double stage_us(int bm, int bn, int per_cu) { return 0.44 + 0.0155e-3 * bm * bn * per_cu; }
+constexpr double kTileUs = 4.0;
+
+struct Shape { int id, bm, bn, per_cu; };
+// shapes that cover an output alone (ids as in launch_shape); per_cu: workgroups whose LDS and
+// registers fit one CU
+constexpr Shape kAlone[] = {{4, 192, 256, 1}, {5, 192, 192, 1}, {6, 192, 128, 1}, {7, 128, 256, 1},
+                            {8, 128, 128, 2}, {9, 64, 256, 1},  {10, 64, 128, 2}};
 
 }  // namespace
 
-BigPlan plan_big(int M, int N, int K, bool swiglu, int splits) {
-    const int C = swiglu ? 128 : 256;
+// The cover whose estimated length is least.  A round of workgroups lasts as long as its tiles, so
+// 256 x 256 tiles win where their rounds are full or nearly so; else their last round goes to
+// smaller tiles, or (few rows, where a round of 256 x 256 tiles is never full) one smaller shape
+// covers everything.  544 rows of the 7B gate/up: 192x192 130 us, 256x256 154; down, K split
+// three ways: 128x128 74 us, 256x256 96.
+static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
+    const int C = swiglu ? 128 : 256, f = swiglu ? 2 : 1;
     const int mt = (M + 255) / 256, nt = (N + C - 1) / C;
     const double stages = (double)K / kBK / splits;
-    // cost of a tile in stage times of a 256 x 256 tile, prologue and epilogue included
-    const double c256 = stages + 4.0, c192 = 0.79 * stages + 3.5, c128 = 0.60 * stages + 3.0;
+    auto tile_us = [&](int bm, int bn) { return stages * stage_us(bm, bn, 1) + kTileUs; };
+    const double c256 = tile_us(256, 256);
     BigPlan best;
     best.m_main = mt;
     best.n_main = nt;
     best.splits = splits;
-    best.cost = makespan((long)mt * nt * splits, c256, 0, 0.0);
+    best.us = makespan((long)mt * nt * splits, c256, 0, 0.0);
     auto offer = [&](const BigPlan &p) {
-        if (p.cost < best.cost * 0.98) best = p;
+        if (p.us < best.us * 0.98) best = p;
     };
-    // the last rows on 128-row tiles
+    // the last rows on 128- or 64-row tiles
     const int rem = M % 256;
-    if (rem > 0 && rem <= 128) {
+    if (M > 256 && rem > 0 && rem <= 128) {
+        const int bm = rem <= 64 ? 64 : 128;
         BigPlan p;
-        p.shape = 1;
+        p.shape = bm == 64 ? 11 : 1;
         p.m_main = M / 256;
-        p.n_main = p.m_main ? nt : 0;
+        p.n_main = nt;
         p.m_alt = 1;
         p.n_alt = nt;
         p.row_alt = M - rem;
         p.splits = splits;
-        p.cost = makespan((long)p.m_main * p.n_main * splits, c256, (long)nt * splits, c128);
+        p.us = makespan((long)p.m_main * nt * splits, c256, (long)nt * splits, tile_us(bm, 256));
         offer(p);
     }
     // columns past the first j column tiles on 192- or 128-wide tiles
     for (int shape = 2; shape <= 3; ++shape) {
-        const int w = (shape == 2 ? 192 : 128) / (swiglu ? 2 : 1);
+        const int w = (shape == 2 ? 192 : 128) / f;
         for (int j = 0; j < nt; ++j) {
             BigPlan p;
             p.shape = shape;
@@ -382,23 +400,70 @@ BigPlan plan_big(int M, int N, int K, bool swiglu, int splits) {
             p.n_alt = (N - j * C + w - 1) / w;
             p.col_alt = j * C;
             p.splits = splits;
-            p.cost = makespan((long)mt * j * splits, c256, (long)mt * p.n_alt * splits, shape == 2 ? c192 : c128);
+            p.us = makespan((long)mt * j * splits, c256, (long)mt * p.n_alt * splits, tile_us(256, w * f));
             offer(p);
         }
+    }
+    for (const Shape &sh : kAlone) {
+        BigPlan p;
+        p.shape = sh.id;
+        p.m_alt = (M + sh.bm - 1) / sh.bm;
+        p.n_alt = (N + sh.bn / f - 1) / (sh.bn / f);
+        p.splits = splits;
+        const long n = (long)p.m_alt * p.n_alt * splits, slots = 256L * sh.per_cu, left = n % slots;
+        const double full = stages * stage_us(sh.bm, sh.bn, sh.per_cu) + kTileUs;
+        p.us = n / slots * full + (left == 0 ? 0.0 : left <= 256 ? tile_us(sh.bm, sh.bn) : full);
+        offer(p);
     }
     return best;
 }
 
-template <int EPI>
+// The search takes a few microseconds; a layer asks for the same four covers as the one before it, so
+// each thread keeps the last ones it computed (a pure function of the sizes).
+BigPlan plan_big(int M, int N, int K, bool swiglu, int splits) {
+    struct Entry { int M = -1, N = 0, K = 0, sw = 0, splits = 0; BigPlan plan; };
+    static thread_local Entry memo[64];
+    const unsigned h = (unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)(splits * 2 + swiglu) * 668265263u;
+    Entry &e = memo[h >> 26];
+    if (e.M != M || e.N != N || e.K != K || e.sw != (int)swiglu || e.splits != splits)
+        e = Entry{M, N, K, (int)swiglu, splits, search_plan(M, N, K, swiglu, splits)};
+    return e.plan;
+}
+
+int big_splits(int M, int N, int K, int max_splits) {
+    int best = 1;
+    double best_us = 0.0;
+    for (int s = 1; s <= max_splits; ++s) {
+        if (s > 1 && (K % kBK || K / s < 512)) continue;
+        // the next row kernel reads every slab, at about 4 TB/s
+        const double us = plan_big(M, N, K, false, s).us + s * ((double)M * N * 4 / 4e6);
+        if (s == 1 || us < best_us) { best = s; best_us = us; }
+    }
+    return best;
+}
+
+template <bool SW>
 static hipError_t launch_shape(const GemmArgs &a, const BigPlan &p, hipStream_t s) {
     const dim3 grid((p.m_main * p.n_main + p.m_alt * p.n_alt) * p.splits), block(64 * kWaves);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, p);
+        return hipGetLastError();
+    };
     switch (p.shape) {
-        case 0: hipLaunchKernelGGL((gemm_big_kernel<EPI, 0, 0, 4, 2>), grid, block, 0, s, a, p); break;
-        case 1: hipLaunchKernelGGL((gemm_big_kernel<EPI, 128, 256, 2, 4>), grid, block, 0, s, a, p); break;
-        case 2: hipLaunchKernelGGL((gemm_big_kernel<EPI, 256, 192, 4, 2>), grid, block, 0, s, a, p); break;
-        default: hipLaunchKernelGGL((gemm_big_kernel<EPI, 256, 128, 4, 2>), grid, block, 0, s, a, p); break;
+        case 0: return go(gemm_big_kernel<SW, true, 0, 0, 4, 2>);
+        case 1: return go(gemm_big_kernel<SW, true, 128, 256, 2, 4>);
+        case 2: return go(gemm_big_kernel<SW, true, 256, 192, 4, 2>);
+        case 3: return go(gemm_big_kernel<SW, true, 256, 128, 4, 2>);
+        case 4: return go(gemm_big_kernel<SW, false, 192, 256, 2, 4>);
+        case 5: return go(gemm_big_kernel<SW, false, 192, 192, 4, 2>);
+        case 6: return go(gemm_big_kernel<SW, false, 192, 128, 4, 2>);
+        case 7: return go(gemm_big_kernel<SW, false, 128, 256, 2, 4>);
+        case 8: return go(gemm_big_kernel<SW, false, 128, 128, 4, 2>);
+        case 9: return go(gemm_big_kernel<SW, false, 64, 256, 2, 4>);
+        case 10: return go(gemm_big_kernel<SW, false, 64, 128, 2, 4>);
+        case 11: return go(gemm_big_kernel<SW, true, 64, 256, 2, 4>);
+        default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // a tile's 256 rows are addressed by 32-bit byte offsets
@@ -409,12 +474,11 @@ bool gemm_big_takes(const GemmArgs &a) {
 hipError_t launch_gemm_big(int epi, const GemmArgs &a, const BigPlan &p, hipStream_t s) {
     if (!gemm_big_takes(a) || a.K / kBK < p.splits || (p.splits > 1 && (epi != EPI_ADD_F32 || !a.partial)))
         return hipErrorInvalidValue;
-    switch (epi) {
-        case EPI_STORE_F32: return launch_shape<EPI_STORE_F32>(a, p, s);
-        case EPI_ADD_F32: return launch_shape<EPI_ADD_F32>(a, p, s);
-        case EPI_SWIGLU: return launch_shape<EPI_SWIGLU>(a, p, s);
-        default: return hipErrorInvalidValue;
-    }
+    if (epi == EPI_SWIGLU) return launch_shape<true>(a, p, s);
+    if (epi != EPI_STORE_F32 && epi != EPI_ADD_F32) return hipErrorInvalidValue;
+    BigPlan q = p;
+    q.add = epi == EPI_ADD_F32;
+    return launch_shape<false>(a, q, s);
 }
 
 }  // namespace orthrus

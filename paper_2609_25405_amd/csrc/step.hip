@@ -29,25 +29,14 @@ struct Layout {
 };
 // split-K slabs of one residual-add projection: at most kMaxSplits fp32 [T][d] slabs
 constexpr int kMaxSplits = 4;
-// QKV projections of at most kQkvSplitRows rows per model, or of more than kQkvSplitMinRows and
-// at most kQkvFusedMaxRows, split K in two (bf16 path): their fp32 partial sums [2][T][qkv_dim]
-// get a region of qkv_slab_rows(T) rows, which the rotation/append kernel sums in split order.
-// Measured on the 7B shape at 64 rows: the split projection and the rotation kernel take
-// 18.6 + 6.9 us against 42.6 us fused (48 whole-head tiles); 8 splits 22.1 + 10.3 us; at 96
-// rows 23.9 + 8.2 us against 44.0 us, at 128 rows 25.8 + 8.4 against 45.1 us; at 384 rows the
-// fused projection is faster (54.5 us against 46.2 + 15.4 us with 4 splits).  At 1024 rows the
-// split projection on 256x256 tiles (192 workgroups) takes 58 us against 79 us for the 128x128
-// whole-head tiles before their fused epilogue (90 us with it in the two-model step)
-constexpr int kQkvSplitRows = 128;
-constexpr int kQkvSplitMinRows = 896;
+// QKV projections (bf16 path) leave fp32 rows, or the partial sums [2][T][qkv_dim] of a K split in
+// two (gemm_qkv_splits), which the rotation/append kernel finishes.  A fused epilogue (whole-head
+// 64x128 or 128x128 tiles that rotate and append themselves) was slower at every size: 7B shape, 64
+// rows 42.6 us against 18.6 + 6.9, 544 rows 59 against 33 + 11, 2048-wide shape 370 rows 28
+// against 14 + 7.  Partial sums of at most kQkvSplitRows rows fit the region of qkv_slab_rows(T).
 constexpr int kQkvSplits = 2;
-// QKV projections of more than kQkvFusedMaxRows rows per model (bf16 path) store fp32 rows
-// from one round of 192x256 or 256x256 tiles and rotate them in the row kernel: whole-head
-// 128x128 tiles with the fused epilogue need more than one round there (7B shape: 1568 rows
-// 138 us fused against 86 + ~12 us; 2048 rows 173 us against 104 + ~15 us)
-constexpr int kQkvFusedMaxRows = 1280;
-size_t qkv_slab_rows(size_t T) { return (size_t)kQkvSplits * std::min<size_t>(T, 2 * kQkvFusedMaxRows); }
-bool qkv_split_rows(int rows) { return rows <= kQkvSplitRows || (rows > kQkvSplitMinRows && rows <= kQkvFusedMaxRows); }
+constexpr int kQkvSplitRows = 2560;
+size_t qkv_slab_rows(size_t T) { return (size_t)kQkvSplits * std::min<size_t>(T, kQkvSplitRows); }
 
 Layout make_layout(const Model &m, size_t T, size_t meta_ints, size_t n_partials) {
     const size_t es = m.cfg.dtype == ORTHRUS_BF16 ? 2 : 4;
@@ -58,8 +47,7 @@ Layout make_layout(const Model &m, size_t T, size_t meta_ints, size_t n_partials
     L.meta = o; o += up(meta_ints * 4);
     L.x = o; o += up(T * d * 4);
     L.act = o; o += up(T * d * es);
-    // fp32 QKV rows for the separate rotation kernel: every row on the fp32 path; on the bf16
-    // path (which rotates in the GEMM epilogue) the split-K partials of small projections
+    // fp32 QKV rows for the rotation kernel, on the bf16 path also the two partial sums of a split
     L.qkv = o; o += up((m.cfg.dtype == ORTHRUS_BF16 ? std::max(T, qkv_slab_rows(T)) : T) * (size_t)m.qkv_dim() * 4);
     L.q = o; o += up(T * (size_t)m.q_dim() * es);
     L.o = o; o += up(T * (size_t)m.q_dim() * es);
@@ -642,12 +630,8 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ra.v_cache[0] = (char *)emb_kv->v_cache + l * e_stride;
         ra.k_cache[1] = (char *)gen_kv->k_cache + l * g_stride;
         ra.v_cache[1] = (char *)gen_kv->v_cache + l * g_stride;
-        // small bf16 projections (decode-only batches) stream their weights, and whole-head tiles
-        // for the fused rotation leave too few workgroups (48 at 64 rows): they split K into fp32
-        // partials, which the rotation/append row kernel sums in split order
-        const int qkv_splits = dt == ORTHRUS_BF16 && qkv_split_rows(max_rows) && d % (kQkvSplits * 64) == 0 &&
-                                       d / kQkvSplits >= 512 && (size_t)kQkvSplits * T <= qkv_slab_rows(T)
-                                   ? kQkvSplits
+        const int qkv_splits = dt == ORTHRUS_BF16 && (size_t)kQkvSplits * T <= qkv_slab_rows(T)
+                                   ? gemm_qkv_splits(max_rows, qkvd, d, concurrent)
                                    : 1;
         if (qkv_splits > 1) {
             for (int gi = 0; gi < n_groups; ++gi) {
@@ -674,40 +658,6 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
                 for (int gi = 0; gi < n_groups; ++gi) RUNG(groups[gi], "rope_append", rope_group(groups[gi]));
             } else {
                 RUN("rope_append", launch_rope_append(dt, ra, s));
-            }
-        } else if (dt == ORTHRUS_BF16 && max_rows <= kQkvFusedMaxRows) {
-            // QKV projection with rotation and cache append in its epilogue
-            for (int gi = 0; gi < n_groups; ++gi) {
-                const Group &g = groups[gi];
-                GemmArgs ga{};
-                ga.A = act + (size_t)g.r0 * d * es;
-                ga.B0 = g.m->layers[l].w_qkv;
-                ga.M = g.r1 - g.r0;
-                ga.N = qkvd;
-                ga.K = d;
-                ga.lda = d;
-                ga.splits = 1;
-                QkvRope &q = ga.rope;
-                q.cs = rope_cs;
-                q.pos = ra.pos;
-                q.seq = ra.seq;
-                q.q_out = qb;
-                for (int i = 0; i < 2; ++i) {
-                    q.k_cache[i] = ra.k_cache[i];
-                    q.v_cache[i] = ra.v_cache[i];
-                    q.block_table[i] = ra.block_table[i];
-                    q.n_pages[i] = ra.n_pages[i];
-                    q.max_blocks[i] = ra.max_blocks[i];
-                }
-                q.row0 = g.r0;
-                q.Te = Te;
-                q.nq = c.n_q_heads;
-                q.nkv = c.n_kv_heads;
-                q.hd = c.head_dim;
-                q.page = c.page_size;
-                q.err = err;
-                if (lora_on(0, g)) RUNG(g, "lora_shrink", lora(0, l, g, act, d, d, ga.lora));
-                RUNG(g, "gemm_qkv_rope", launch_gemm(dt, EPI_QKV_ROPE, ga, g.st));
             }
         } else {
             for (int gi = 0; gi < n_groups; ++gi) {

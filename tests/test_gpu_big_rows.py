@@ -1,7 +1,7 @@
-"""Projections of more than 896 rows (the 256-row tiles of the large kernel and its second tile
-shapes) against the float64 oracle, at row counts on and beside the edges of its tiles: one row past
-the smallest batch it takes, a last row tile of one row, of exactly 128 and of 129 rows, whole
-tiles, and enough rows for several rounds; with LoRA adapters on part of the rows (ranks 16 and 48,
+"""Projections of more than 128 rows (the large kernel's tile shapes) against the float64 oracle, at
+row counts on and beside the edges of its tiles: one row past the smallest batch it takes, row
+counts that its covers give to 64-, 128- and 192-row tiles, a last row tile of one row, of exactly
+64, 128 and of 129 rows, whole tiles, and enough rows for several rounds; with LoRA adapters on part of the rows (ranks 16 and 48,
 so that a 32-column step of the update ends inside and past an adapter's block)."""
 import numpy as np
 import pytest
@@ -20,7 +20,7 @@ def _need_gpu(request):
     print(f"\n[case] {request.node.name}", flush=True)
 
 
-@pytest.mark.parametrize("rows,rank", [(897, 0), (1025, 0), (1152, 16), (1281, 48), (1536, 0), (2049, 0)])
+@pytest.mark.parametrize("rows,rank", [(129, 0), (193, 16), (257, 0), (449, 48), (640, 0), (832, 0), (897, 0), (1025, 0), (1088, 0), (1152, 16), (1281, 48), (1536, 0), (2049, 0)])
 def test_rows(rows, rank):
     cfg = ModelConfig(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=2816, vocab=512,
                       dtype="bf16")
