@@ -196,15 +196,22 @@ __device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, 
 
     // LoRA update: acc += U B^T for rows below lora.rows (split 0), 32 columns of U per MFMA step
     // (U as its bf16 rounding plus remainder, two MFMAs), operands straight from global memory; a
-    // fragment's 8 columns lie in one adapter's block because ranks are multiples of 16
+    // fragment's 8 columns lie in one adapter's block because ranks are multiples of 16.  The four
+    // adapters' pointers are selected in registers: indexed by lane they would be vector loads from
+    // the kernel arguments, microseconds each
     if (a.lora.n > 0 && split == 0 && m0 < a.lora.rows) {
         const LoraGemm &L = a.lora;
         const int ldu = L.n * L.r;
         const bf16x8 zero = {};
+        auto pick = [](const void *const (&b)[kMaxStepAdapters], int j) {
+            static_assert(kMaxStepAdapters == 4, "four pointers");
+            return (const bf16 *)(j == 0 ? b[0] : j == 1 ? b[1] : j == 2 ? b[2] : b[3]);
+        };
         for (int c0 = 0; c0 < ldu; c0 += 32) {
             const int c = c0 + 8 * (lane >> 4);
             const bool in = c < ldu;
             const int j = in ? c / L.r : 0, kk = in ? c % L.r : 0;
+            const bf16 *const b0 = pick(L.b0, j), *const b1 = SW ? pick(L.b1, j) : nullptr;
             bf16x8 ua[FM], ul[FM];
 #pragma unroll
             for (int mi = 0; mi < FM; ++mi) {
@@ -219,10 +226,10 @@ __device__ __forceinline__ void big_tile(const GemmArgs &a, char *smem, int m0, 
                 const bf16 *src;
                 if constexpr (SW) {
                     col = n0 + wn * (TN / 2) + (ni % (FN / 2)) * 16 + (lane & 15);
-                    src = (const bf16 *)(ni < FN / 2 ? L.b0[j] : L.b1[j]);
+                    src = ni < FN / 2 ? b0 : b1;
                 } else {
                     col = n0 + wn * TN + ni * 16 + (lane & 15);
-                    src = (const bf16 *)L.b0[j];
+                    src = b0;
                 }
                 const bf16x8 ub = in ? *(const bf16x8 *)(src + (size_t)min(col, a.N - 1) * L.r + kk) : zero;
 #pragma unroll

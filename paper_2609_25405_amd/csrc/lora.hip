@@ -2,69 +2,72 @@
 // U B^T, runs inside the projection GEMM's epilogue).  The shared-backbone deployment of the
 // paper adapts the generator into the embedding model this way (Section 2, parameter sharing).
 //
-// bf16 path: one workgroup per 32 rows x 64 columns of U, eight waves splitting K eight ways,
-// each accumulating a 32x64 fp32 block on v_mfma_f32_32x32x16_bf16 with operands loaded straight
-// from global memory (x rows and A rows are both K-contiguous, the MFMA operand layout); the
-// eight partial blocks are summed in LDS in a fixed order (deterministic), scaled, masked to the
+// bf16 path: one workgroup per 16 rows x 16 columns of U (so one adapter), eight waves splitting K
+// eight ways on v_mfma_f32_16x16x32_bf16 with operands loaded straight from global memory, eight K
+// steps in flight; a block none of whose rows names its adapter writes zeros and ends.  The eight
+// partial blocks are summed in LDS in a fixed order (deterministic), scaled, masked to the
 // row's adapter and stored as two bf16 arrays, the rounding of each value and its remainder, so
 // the expand can use U to about 16 significant bits (a single bf16 U doubles the adapter
-// path's rounding error at 7B shapes).  fp32 path: one thread per output, plain dot products.
+// path's rounding error at 7B shapes).  The launch is a chain of load latencies, so workgroups and
+// loads in flight count: 512 rows, four adapters of rank 16, 48 us per projection on 16 workgroups
+// of 32 x 64 with one step in flight.  fp32 path: one thread per output, plain dot products.
 #include "common.hpp"
 
 namespace orthrus {
 
 namespace {
 
-__global__ __launch_bounds__(512) void lora_shrink_bf16(LoraShrink p) {
-    __shared__ float red[8][32][65];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.x * 32, c0 = blockIdx.y * 64;
-    const int ldu = p.n * p.r;
-    const int kw = p.K / 8;                        // this wave's slice of K (a multiple of 16)
-    const int k_begin = wave * kw + 8 * (lane >> 5);
-    const int row = min(m0 + (lane & 31), p.rows - 1);
-    const bf16 *xr = (const bf16 *)p.x + (size_t)row * p.ldx + k_begin;
-    const bf16 *br[2];
-    bool bok[2];
-#pragma unroll
-    for (int f = 0; f < 2; ++f) {
-        const int col = c0 + f * 32 + (lane & 31);
-        bok[f] = col < ldu;
-        const int j = bok[f] ? col / p.r : 0, kk = bok[f] ? col % p.r : 0;
-        br[f] = (const bf16 *)p.a[j] + (size_t)kk * p.K + k_begin;
+static_assert(kMaxStepAdapters == 4, "pointers are selected from four");
+constexpr int kShrinkWaves = 8, kShrinkAhead = 8;
+
+__global__ __launch_bounds__(64 * kShrinkWaves) void lora_shrink_bf16(LoraShrink p) {
+    __shared__ float red[kShrinkWaves][16][17];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = blockIdx.x * 16, c0 = blockIdx.y * 16, ldu = p.n * p.r;
+    const int j = c0 / p.r, kk = c0 % p.r;                 // ranks are multiples of 16
+    const int rr = (threadIdx.x >> 4) & 15, cc = threadIdx.x & 15;
+    const size_t o = (size_t)(m0 + rr) * ldu + c0 + cc;
+    const bool mine = m0 + (lane & 15) < p.rows && p.row_adapter[min(m0 + (lane & 15), p.rows - 1)] == j;
+    if (__ballot(mine) == 0) {
+        if (threadIdx.x < 256 && m0 + rr < p.rows) {
+            ((bf16 *)p.u)[o] = (bf16)0.f;
+            ((bf16 *)p.u_lo)[o] = (bf16)0.f;
+        }
+        return;
     }
-    f32x16 acc[2];
+    const int steps = p.K / 32;
+    const int s0 = wave * steps / kShrinkWaves, s1 = (wave + 1) * steps / kShrinkWaves;
+    const void *a = j == 0 ? p.a[0] : j == 1 ? p.a[1] : j == 2 ? p.a[2] : p.a[3];
+    const bf16 *xr = (const bf16 *)p.x + (size_t)min(m0 + (lane & 15), p.rows - 1) * p.ldx + 8 * (lane >> 4);
+    const bf16 *ar = (const bf16 *)a + (size_t)(kk + (lane & 15)) * p.K + 8 * (lane >> 4);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s = s0; s < s1; s += kShrinkAhead) {
+        bf16x8 xa[kShrinkAhead], aa[kShrinkAhead];
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+        for (int i = 0; i < kShrinkAhead; ++i) {
+            if (s + i >= s1) break;
+            xa[i] = *(const bf16x8 *)(xr + 32 * (s + i));
+            aa[i] = *(const bf16x8 *)(ar + 32 * (s + i));
+        }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
-    const bf16x8 zero = {};
-    for (int k = 0; k < kw; k += 16) {
-        const bf16x8 xa = *(const bf16x8 *)(xr + k);
-#pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const bf16x8 bb = bok[f] ? *(const bf16x8 *)(br[f] + k) : zero;
-            acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa, bb, acc[f], 0, 0, 0);
+        for (int i = 0; i < kShrinkAhead; ++i) {
+            if (s + i >= s1) break;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[i], aa[i], acc, 0, 0, 0);
         }
     }
-    // D layout: column lane % 32, row 8 (e / 4) + 4 (lane / 32) + e % 4
+    // lane holds column lane % 16, rows 4 (lane / 16) + e
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            red[wave][(e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)][f * 32 + (lane & 31)] = acc[f][e];
+    for (int e = 0; e < 4; ++e) red[wave][(lane >> 4) * 4 + e][lane & 15] = acc[e];
     __syncthreads();
-    for (int o = threadIdx.x; o < 32 * 64; o += 512) {
-        const int rr = o >> 6, cc = o & 63, grow = m0 + rr, gcol = c0 + cc;
-        if (grow >= p.rows || gcol >= ldu) continue;
+    if (threadIdx.x < 256 && m0 + rr < p.rows) {
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) sum += red[w][rr][cc];
-        const int j = gcol / p.r;
-        const float v = p.row_adapter[grow] == j ? sum * p.scale[j] : 0.f;
+        for (int w = 0; w < kShrinkWaves; ++w) sum += red[w][rr][cc];
+        const float scale = j == 0 ? p.scale[0] : j == 1 ? p.scale[1] : j == 2 ? p.scale[2] : p.scale[3];
+        const float v = p.row_adapter[m0 + rr] == j ? sum * scale : 0.f;
         const bf16 hi = (bf16)v;
-        ((bf16 *)p.u)[(size_t)grow * ldu + gcol] = hi;
-        ((bf16 *)p.u_lo)[(size_t)grow * ldu + gcol] = (bf16)(v - to_f32<bf16>(hi));
+        ((bf16 *)p.u)[o] = hi;
+        ((bf16 *)p.u_lo)[o] = (bf16)(v - to_f32<bf16>(hi));
     }
 }
 
@@ -90,8 +93,8 @@ hipError_t launch_lora_shrink(int dtype, const LoraShrink &p, hipStream_t s) {
     if (p.rows <= 0 || p.n <= 0) return hipSuccess;
     if (dtype == 1) {
         if (p.K % 128 || p.r % 16) return hipErrorInvalidValue;
-        dim3 grid((p.rows + 31) / 32, (p.n * p.r + 63) / 64);
-        hipLaunchKernelGGL(lora_shrink_bf16, grid, dim3(512), 0, s, p);
+        dim3 grid((p.rows + 15) / 16, p.n * p.r / 16);
+        hipLaunchKernelGGL(lora_shrink_bf16, grid, dim3(64 * kShrinkWaves), 0, s, p);
     } else {
         hipLaunchKernelGGL(lora_shrink_f32, dim3(p.rows), dim3(256), 0, s, p);
     }
