@@ -473,7 +473,9 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         if (a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (big) {
             const BigPlan p = plan_big(a.M, a.N, a.K, true, 1);
-            if (a.M > 256 || p.us < stream256_us(2 * a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
+            // (plan_big's estimate is for weights that several row tiles share; read once, from HBM, they
+            // take a fifth longer: 160 / 256 rows of the 7B gate/up est. 57 / 65, measured 64 / 80 us)
+            if (a.M > 256 || 1.2 * p.us < stream256_us(2 * a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
         }
         if (a.M <= 256) return run_bf16<256, 128, 4, 2, EPI, 64, 3, 3, true>(a, s);
         if (a.M > 896) {

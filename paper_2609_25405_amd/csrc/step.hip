@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "gemm_skinny.hpp"
 #include "model.hpp"
 #include "orthrus.h"
 #include "plan.hpp"
@@ -590,7 +591,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     // rotation/append, attention and merge run on the group's stream over its own rows, the
     // planner's items of its chunks (and, for the generator, the decode rows) and its merge
     // entries, so the groups' layer chains proceed independently
-    auto rope_group = [&](const Group &g) -> hipError_t {
+    auto rope_rows = [&](const Group &g) {
         RopeArgs r = ra;
         r.qkv = ra.qkv + (size_t)g.r0 * qkvd;
         r.cs = ra.cs ? ra.cs + (size_t)g.r0 * (c.head_dim / 2) : nullptr;
@@ -599,8 +600,9 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         r.seq = ra.seq + g.r0;
         r.T = g.r1 - g.r0;
         r.Te = std::max(0, std::min(Te - g.r0, r.T));
-        return launch_rope_append(dt, r, g.st);
+        return r;
     };
+    auto rope_group = [&](const Group &g) { return launch_rope_append(dt, rope_rows(g), g.st); };
     const int merges_gen = p.n_split_prefill - p.n_merge_emb;
     auto attn_group = [&](int gi, bool combine) -> hipError_t {
         AttnArgs ag = aa;
@@ -620,12 +622,40 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         return combine ? launch_attn_combine(dt, ag, n_dec, groups[gi].st) : launch_attention(dt, ag, groups[gi].st);
     };
 
-    for (int l = 0; l < c.n_layers; ++l) {
-        if (l > 0) {
-            for (int gi = 0; gi < n_groups; ++gi)
-                RUNG(groups[gi], "rmsnorm", norm(false, groups[gi], groups[gi].m->layers[l].attn_norm));
-            pending = 0;
+    // Projections of gemm_skinny.hip (bf16, no adapters, every row group of at most kSkinnyRows rows):
+    // they finish their rows themselves (residual add, rotation and append), so no slabs of
+    // theirs are pending, and where it pays they also norm the rows of x
+    auto skinny = [&](int N, int K) { return dt == ORTHRUS_BF16 && p.n_used == 0 && skinny_takes(max_rows, N, K); };
+    const bool sk_qkv = skinny(qkvd, d), sk_o = skinny(d, qd), sk_gu = skinny(2 * F, d), sk_down = skinny(d, F);
+    auto skinny_args = [&](const Group &g, const void *A, int lda, const void *B0, int N, int K) {
+        SkinnyArgs sa{};
+        sa.A = (const char *)A + (size_t)g.r0 * lda * es;
+        sa.lda = lda;
+        sa.B0 = B0;
+        sa.M = g.r1 - g.r0;
+        sa.N = N;
+        sa.K = K;
+        return sa;
+    };
+    // the norm of the rows of x before a projection: left to the projection's launch (true) or launched
+    auto norm_rows = [&](bool by_launch, auto &&gain) -> int {
+        if (!by_launch) {
+            for (int gi = 0; gi < n_groups; ++gi) RUNG(groups[gi], "rmsnorm", norm(false, groups[gi], gain(groups[gi])));
         }
+        pending = 0;
+        return ORTHRUS_OK;
+    };
+    auto take_x = [&](SkinnyArgs &sa, const Group &g, const float *gain) {
+        sa.A = nullptr;
+        sa.x = x + (size_t)g.r0 * d;
+        sa.gain = gain;
+        sa.eps = c.rms_eps;
+    };
+
+    for (int l = 0; l < c.n_layers; ++l) {
+        // layer 0's rows were normed with the gather
+        const bool qkv_norms = l > 0 && sk_qkv && pending == 0 && skinny_norms(max_rows, qkvd, d);
+        if (l > 0) SYNC_GROUPS(norm_rows(qkv_norms, [&](const Group &g) { return g.m->layers[l].attn_norm; }));
         ra.k_cache[0] = (char *)emb_kv->k_cache + l * e_stride;
         ra.v_cache[0] = (char *)emb_kv->v_cache + l * e_stride;
         ra.k_cache[1] = (char *)gen_kv->k_cache + l * g_stride;
@@ -633,7 +663,15 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         const int qkv_splits = dt == ORTHRUS_BF16 && (size_t)kQkvSplits * T <= qkv_slab_rows(T)
                                    ? gemm_qkv_splits(max_rows, qkvd, d, concurrent)
                                    : 1;
-        if (qkv_splits > 1) {
+        if (sk_qkv) {
+            for (int gi = 0; gi < n_groups; ++gi) {
+                const Group &g = groups[gi];
+                SkinnyArgs sa = skinny_args(g, act, d, g.m->layers[l].w_qkv, qkvd, d);
+                if (qkv_norms) take_x(sa, g, g.m->layers[l].attn_norm);
+                sa.rope = rope_rows(g);
+                RUNG(g, "gemm_qkv_rope", launch_skinny(SKINNY_QKV, sa, g.st));
+            }
+        } else if (qkv_splits > 1) {
             for (int gi = 0; gi < n_groups; ++gi) {
                 const Group &g = groups[gi];
                 GemmArgs ga{};
@@ -687,31 +725,47 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
             if (p.n_split_rows > 0 || p.n_split_prefill > 0)
                 RUN("attn_combine", launch_attn_combine(dt, aa, p.n_split_rows, s));
         }
-        int splits = add_splits(qd);
+        // residual-add projection of the rows of `in` [.][K]: added to x, or left pending as slabs
+        auto add_rows = [&](const char *name, bool sk, int site, const char *in, int K, auto &&weights) -> int {
+            const int splits = sk ? 1 : add_splits(K);
+            for (int gi = 0; gi < n_groups; ++gi) {
+                const Group &g = groups[gi];
+                const void *B = weights(g.m->layers[l]);
+                if (sk) {
+                    SkinnyArgs sa = skinny_args(g, in, K, B, d, K);
+                    sa.out = x + (size_t)g.r0 * d;
+                    sa.ldo = d;
+                    RUNG(g, name, launch_skinny(SKINNY_ADD, sa, g.st));
+                    continue;
+                }
+                LoraGemm lg{};
+                if (lora_on(site, g)) RUNG(g, "lora_shrink", lora(site, l, g, in, K, K, lg));
+                RUNG(g, name, add_proj(g, in, K, B, K, splits, lg));
+            }
+            pending = splits > 1 ? splits : 0;
+            return ORTHRUS_OK;
+        };
+        SYNC_GROUPS(add_rows("gemm_o", sk_o, 1, ob, qd, [](const orthrus_layer_weights &lw) { return lw.w_o; }));
+        const bool gu_norms = sk_gu && pending == 0 && skinny_norms(max_rows, 2 * F, d);
+        SYNC_GROUPS(norm_rows(gu_norms, [&](const Group &g) { return g.m->layers[l].mlp_norm; }));
         for (int gi = 0; gi < n_groups; ++gi) {
-            const orthrus_layer_weights &lw = groups[gi].m->layers[l];
+            const Group &g = groups[gi];
+            const orthrus_layer_weights &lw = g.m->layers[l];
+            if (sk_gu) {
+                SkinnyArgs sa = skinny_args(g, act, d, lw.w_gate, F, d);
+                if (gu_norms) take_x(sa, g, lw.mlp_norm);
+                sa.B1 = lw.w_up;
+                sa.out = ub + (size_t)g.r0 * F * es;
+                sa.ldo = F;
+                RUNG(g, "gemm_gate_up", launch_skinny(SKINNY_SWIGLU, sa, g.st));
+                continue;
+            }
             LoraGemm lg{};
-            if (lora_on(1, groups[gi])) RUNG(groups[gi], "lora_shrink", lora(1, l, groups[gi], ob, qd, qd, lg));
-            RUNG(groups[gi], "gemm_o", add_proj(groups[gi], ob, qd, lw.w_o, qd, splits, lg));
+            if (lora_on(2, g)) RUNG(g, "lora_shrink", lora(2, l, g, act, d, d, lg));
+            RUNG(g, "gemm_gate_up", gemm(EPI_SWIGLU, g, act, d, lw.w_gate, lw.w_up, ub, F, es, F, d, lg));
         }
-        pending = splits > 1 ? splits : 0;
-        for (int gi = 0; gi < n_groups; ++gi)
-            RUNG(groups[gi], "rmsnorm", norm(false, groups[gi], groups[gi].m->layers[l].mlp_norm));
-        pending = 0;
-        for (int gi = 0; gi < n_groups; ++gi) {
-            const orthrus_layer_weights &lw = groups[gi].m->layers[l];
-            LoraGemm lg{};
-            if (lora_on(2, groups[gi])) RUNG(groups[gi], "lora_shrink", lora(2, l, groups[gi], act, d, d, lg));
-            RUNG(groups[gi], "gemm_gate_up", gemm(EPI_SWIGLU, groups[gi], act, d, lw.w_gate, lw.w_up, ub, F, es, F, d, lg));
-        }
-        splits = add_splits(F);
-        for (int gi = 0; gi < n_groups; ++gi) {
-            const orthrus_layer_weights &lw = groups[gi].m->layers[l];
-            LoraGemm lg{};
-            if (lora_on(3, groups[gi])) RUNG(groups[gi], "lora_shrink", lora(3, l, groups[gi], ub, F, F, lg));
-            RUNG(groups[gi], "gemm_down", add_proj(groups[gi], ub, F, lw.w_down, F, splits, lg));
-        }
-        pending = splits > 1 ? splits : 0;  // added by the next layer's norm or the final norm
+        // slabs left pending here are added by the next layer's norm or the final norm
+        SYNC_GROUPS(add_rows("gemm_down", sk_down, 3, ub, F, [](const orthrus_layer_weights &lw) { return lw.w_down; }));
     }
 
     SYNC_GROUPS(join());
@@ -765,7 +819,21 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ga.lda = d;
         ga.ldo = gen->cfg.vocab;
         ga.splits = 1;
-        RUN("lm_head", launch_gemm(dt, EPI_STORE_F32, ga, s));
+        if (dt == ORTHRUS_BF16 && skinny_takes(p.n_lm, ga.N, d)) {
+            SkinnyArgs sa{};
+            sa.A = ga.A;
+            sa.B0 = ga.B0;
+            sa.b_blocked = ga.b_blocked;
+            sa.out = ga.out;
+            sa.M = ga.M;
+            sa.N = ga.N;
+            sa.K = ga.K;
+            sa.lda = ga.lda;
+            sa.ldo = ga.ldo;
+            RUN("lm_head", launch_skinny(SKINNY_STORE, sa, s));
+        } else {
+            RUN("lm_head", launch_gemm(dt, EPI_STORE_F32, ga, s));
+        }
     }
     return ORTHRUS_OK;
 #undef RUN
