@@ -106,26 +106,26 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
 
 // ------------------------------------------------------------------ decode split, bf16 path
 // A split is walked in chunks of CP pages (kDecodeChunkPages = 8 pages, 128 keys, in the combined
-// kernel; 4 in the decode-only kernel); each wave owns CP / 4 pages of a chunk.  Loads are branch-free (invalid or absent pages read page 0 and are masked) and
+// kernel; 4 in the decode-only kernel); each wave owns CP / NW pages of a chunk.  Loads are branch-free (invalid or absent pages read page 0 and are masked) and
 // software-pipelined across chunks: the next chunk's K lines go out as soon as this chunk's
 // scores are taken, its V lines as soon as this chunk's P V is done, and page ids two chunks
 // ahead, so the memory pipe stays busy while the wave computes.  Each wave keeps an online
-// softmax (max, sum, output) over its keys of all chunks; the four waves merge once at the end.
-template <int HD, int G, int CP = kDecodeChunkPages>
+// softmax (max, sum, output) over its keys of all chunks; the NW waves merge once at the end.
+template <int HD, int G, int CP = kDecodeChunkPages, int NW = 4>
 __device__ void decode_item_bf16(const AttnArgs &a, const int32_t *it, char *smem) {
     constexpr int KL = HD / 32;     // 16-byte loads per lane per page, for K and for V
     constexpr int QD = HD / 4;      // head dims per lane in the score pass (4 lanes per key)
     constexpr int VD = HD / 64;     // head dims per lane in the value pass
-    constexpr int PPW = CP / 4;                            // pages per wave per chunk
+    constexpr int PPW = CP / NW;                           // pages per wave per chunk
     constexpr int KPW = PPW * kPage;                       // keys per wave per chunk
     constexpr int CHUNK = CP * kPage;                      // keys per chunk
-    uint32_t *pk_all = (uint32_t *)smem;                   // [4 waves][KPW / 2][G] bf16 weight pairs
-    float *mw = (float *)(pk_all + 4 * (KPW / 2) * G);     // [4][G] wave maxima
-    float *lw = mw + 4 * G;                                // [4][G] wave sums
-    float *part = lw + 4 * G;                              // [4][G][HD] wave outputs
+    uint32_t *pk_all = (uint32_t *)smem;                   // [NW waves][KPW / 2][G] bf16 weight pairs
+    float *mw = (float *)(pk_all + NW * (KPW / 2) * G);    // [NW][G] wave maxima
+    float *lw = mw + NW * G;                               // [NW][G] wave sums
+    float *part = lw + NW * G;                             // [NW][G][HD] wave outputs
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t *qs = (uint32_t *)(part + 4 * G * HD) + wave * (G * HD / 2);  // wave's copy of q
+    uint32_t *qs = (uint32_t *)(part + NW * G * HD) + wave * (G * HD / 2);  // wave's copy of q
     const int j = it[IT_INDEX], g = it[IT_KVHEAD];
     const int k0 = it[IT_KEY_BEGIN], k1 = it[IT_KEY_END], pslot = it[IT_PARTIAL];
     const int nk = k1 - k0;
@@ -138,16 +138,16 @@ __device__ void decode_item_bf16(const AttnArgs &a, const int32_t *it, char *sme
     const size_t page_bytes = (size_t)a.nkv * kPage * HD * 2;
     const int kin = lane >> 2, qtr = lane & 3;
 
-    // page ids of chunk c for this wave (pages c * CP + wave + 4 i), raw
+    // page ids of chunk c for this wave (pages c * CP + wave + NW i), raw
     auto load_pages = [&](int c, int (&pg)[PPW]) {
 #pragma unroll
-        for (int i = 0; i < PPW; ++i) pg[i] = bt[min(c * CP + wave + 4 * i, n_pg - 1)];
+        for (int i = 0; i < PPW; ++i) pg[i] = bt[min(c * CP + wave + NW * i, n_pg - 1)];
     };
     // range check: absent pages (past the split) and bad ids read page 0 and are masked later
     auto check_pages = [&](int c, int (&pg)[PPW], bool (&ok)[PPW]) {
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
-            const bool present = c * CP + wave + 4 * i < n_pg;
+            const bool present = c * CP + wave + NW * i < n_pg;
             ok[i] = present && pg[i] >= 0 && pg[i] < pv.n_pages;
             if (present && !ok[i] && lane == 0) flag_error(a.err, ORTHRUS_DEVERR_PAGE);
             pg[i] = ok[i] ? pg[i] : 0;
@@ -217,7 +217,7 @@ __device__ void decode_item_bf16(const AttnArgs &a, const int32_t *it, char *sme
             for (int cc = 0; cc < QD / 8; ++cc) qh[cc] = *(const u32x4 *)(qs + h * (HD / 2) + qtr * (QD / 2) + 4 * cc);
 #pragma unroll
             for (int i = 0; i < PPW; ++i) {
-                const bool vis = ok_cur[i] && cbase + (wave + 4 * i) * kPage + kin < nk;
+                const bool vis = ok_cur[i] && cbase + (wave + NW * i) * kPage + kin < nk;
                 float d2 = 0.f;
 #pragma unroll
                 for (int cc = 0; cc < KL; ++cc)
@@ -266,7 +266,7 @@ __device__ void decode_item_bf16(const AttnArgs &a, const int32_t *it, char *sme
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             // positions of page i inside the split (0 when the page is absent or invalid)
-            const int valid = ok_cur[i] ? min(kPage, nk - cbase - (wave + 4 * i) * kPage) : 0;
+            const int valid = ok_cur[i] ? min(kPage, nk - cbase - (wave + NW * i) * kPage) : 0;
 #pragma unroll
             for (int d = 0; d < VD; ++d) {
 #pragma unroll
@@ -307,15 +307,15 @@ __device__ void decode_item_bf16(const AttnArgs &a, const int32_t *it, char *sme
 #pragma unroll
         for (int d = 0; d < VD; ++d) part[(wave * G + h) * HD + lane * VD + d] = acc[h][d];
     __syncthreads();
-    // ---- merge the four waves in a fixed order
-    for (int o = tid; o < G * HD; o += 256) {
+    // ---- merge the waves in a fixed order
+    for (int o = tid; o < G * HD; o += 64 * NW) {
         const int h = o / HD, d = o % HD;
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) M = fmaxf(M, mw[w * G + h]);
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w * G + h]);
         float L = 0.f, sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < NW; ++w) {
             const float sc_w = mw[w * G + h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w * G + h] - M);
             L += lw[w * G + h] * sc_w;
             sum += part[(w * G + h) * HD + d] * sc_w;
@@ -923,9 +923,9 @@ __device__ void prefill_item_mfma(const AttnArgs &a, const int32_t *it, char *sm
 }
 
 // LDS of a bf16 decode item walked in chunks of CP pages
-template <int HD, int G, int CP>
+template <int HD, int G, int CP, int NW = 4>
 constexpr size_t decode_smem() {
-    return (4 * (CP * kPage / 4 / 2) * G + 8 * G + 4 * G * HD + 4 * G * HD / 2) * 4;
+    return (CP * kPage / 2 * G + 2 * NW * G + NW * G * HD + NW * G * HD / 2) * 4;
 }
 
 template <bool BF16, int HD, int G>
@@ -959,6 +959,18 @@ template <int HD, int G>
 __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[decode_smem<HD, G, kDecodeOnlyChunkPages>()];
     decode_item_bf16<HD, G, kDecodeOnlyChunkPages>(a, a.items + kItemInts * blockIdx.x, smem);
+}
+
+// The same for launches of few items (at most one workgroup a CU) with long key runs: sixteen waves, one
+// page each, so an item walks 256 keys at a time instead of 64 (one row of 700 keys over 8 KV heads
+// 17.8 -> 13.3 us, 16 rows of 300 to 1000 keys 23.0 -> 17.4).  Runs of a few chunks gain nothing: their
+// time is the loads before the first keys and the merge (4 rows of 100 to 300 keys 9.6 us, 10.3 with
+// sixteen waves).
+constexpr int kDecodeWideWaves = 16, kDecodeWideKeys = 384;
+template <int HD, int G>
+__global__ __launch_bounds__(64 * kDecodeWideWaves) void attn_decode_wide_kernel(AttnArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem[decode_smem<HD, G, kDecodeWideWaves, kDecodeWideWaves>()];
+    decode_item_bf16<HD, G, kDecodeWideWaves, kDecodeWideWaves>(a, a.items + kItemInts * blockIdx.x, smem);
 }
 
 // Merge key-range partials in split order: M = max m_s, L = sum l_s 2^(m_s - M),
@@ -1044,7 +1056,9 @@ hipError_t run(const AttnArgs &a, int n_decode, bool combine, hipStream_t s) {
         return hipGetLastError();
     }
     if (a.n_items <= 0) return hipSuccess;
-    if (BF16 && a.n_prefill == 0)
+    if (BF16 && a.n_prefill == 0 && a.n_items <= 256 && a.dec_keys > kDecodeWideKeys)
+        hipLaunchKernelGGL((attn_decode_wide_kernel<HD, G>), dim3(a.n_items), dim3(64 * kDecodeWideWaves), 0, s, a);
+    else if (BF16 && a.n_prefill == 0)
         hipLaunchKernelGGL((attn_decode_kernel<HD, G>), dim3(a.n_items), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL((attn_kernel<BF16, HD, G>), dim3(a.n_items), dim3(256), 0, s, a);

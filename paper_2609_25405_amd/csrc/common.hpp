@@ -164,6 +164,7 @@ struct AttnArgs {
     // n_prefill: prefill items at the head of `items` (0: decode items only, served by the
     // decode-only kernel on the bf16 path); n_items: all items of the launch
     int n_prefill, n_items, n_combine, Te, nq, nkv, hd, page;
+    int dec_keys;             // keys of the longest decode item
     int *err;
 };
 hipError_t launch_attention(int dtype, const AttnArgs &a, hipStream_t s);

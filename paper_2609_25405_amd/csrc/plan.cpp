@@ -263,6 +263,7 @@ int plan_step(const Model &emb, const Model &gen, const orthrus_batch &b, const 
                                                 const std::array<int32_t, kItemInts> &y) {
         return x[IT_KEY_END] - x[IT_KEY_BEGIN] > y[IT_KEY_END] - y[IT_KEY_BEGIN];
     });
+    if (!dec.empty()) p.dec_keys = dec[0][IT_KEY_END] - dec[0][IT_KEY_BEGIN];
     // prefill pieces take partial slots after the decode rows': piece k of a split tile holds
     // its qrows tokens in consecutive slots, pieces of one tile qrows slots apart
     std::vector<int32_t> items(kItemInts * pre.size());

@@ -63,6 +63,7 @@ struct StepPlan {
     int T = 0, Te = 0, Tg = 0, D = 0, n_chunks = 0, n_gen = 0;
     bool shared_kv = true;
     int n_prefill = 0, n_decode_items = 0, n_partials = 0, n_split_rows = 0;
+    int dec_keys = 0;         // keys of the longest decode item
     int n_split_prefill = 0;  // prefill items cut along keys (merge entries at off_combine)
     // two distinct models: the first n_pre_emb prefill items and the first n_merge_emb merge
     // entries belong to embedding chunks (the embedding model's rows), the rest to generation

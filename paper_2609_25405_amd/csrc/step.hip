@@ -557,6 +557,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     aa.nkv = c.n_kv_heads;
     aa.hd = c.head_dim;
     aa.page = c.page_size;
+    aa.dec_keys = p.dec_keys;
     aa.err = err;
     aa.block_table[0] = emb_kv->block_table;
     aa.block_table[1] = gen_kv->block_table;
