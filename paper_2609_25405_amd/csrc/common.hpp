@@ -189,6 +189,8 @@ struct PoolArgs {
     float *hidden;            // buffered-head output [rows][d] fp32
     int n_chunks, Te, d;
     int n_emb_rows, n_lm;     // final-norm launch: embedding rows [0, n_emb_rows), lm_rows
+    float *part;              // launch_final_pool: [Te / 4][d] fp32 sums of chunk slices
+    int max_len, max_slices;  // launch_final_pool: the longest summed or buffered chunk (max_slices set there)
     float eps;
     int *err;
 };
@@ -201,8 +203,10 @@ hipError_t launch_argmax(const float *logits, int rows, int vocab, int32_t *out,
 // their row's final norm themselves (adding npend slabs); with any_rows, mean, weighted-mean and
 // buffered chunks are handled too and need launch_final_rows over the embedding rows first.
 hipError_t launch_pool(const PoolArgs &a, bool any_rows, hipStream_t s);
-// both at once when no chunk needs every embedding row's norm (n_emb_rows == 0): the LM rows'
-// final norm and the single-row pooler in one launch
-hipError_t launch_final_and_pool(int dtype, const PoolArgs &a, hipStream_t s);
+// d <= 8192: final norm of the LM rows and the whole pooler (n_emb_rows unused); slices: some summed
+// chunk is longer than one slice or some chunk is buffered
+bool final_pool_takes(int d);
+constexpr int kPoolSliceRows = 8;
+hipError_t launch_final_pool(int dtype, const PoolArgs &a, bool slices, hipStream_t s);
 
 }  // namespace orthrus

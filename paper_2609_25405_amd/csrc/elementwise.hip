@@ -539,29 +539,29 @@ __device__ void pool_rows_block(const PoolArgs &a, int ci, float *red) {
             return q;
         };
         float ss = 0.f;
-        for (int v = threadIdx.x; v < nv; v += 256) {
+        for (int v = threadIdx.x; v < nv; v += blockDim.x) {
             const float4 q = row(v);
             ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
         }
         const float inv = rsqrtf(block_sum(ss, red) / (float)a.d + a.eps);
-        for (int v = threadIdx.x; v < nv; v += 256) {
+        for (int v = threadIdx.x; v < nv; v += blockDim.x) {
             const float4 q = row(v), g = load4(a.gain + 4 * v);
             store4(S + 4 * v, float4{q.x * inv * g.x, q.y * inv * g.y, q.z * inv * g.z, q.w * inv * g.w});
         }
     } else if (pool == ORTHRUS_POOL_LAST && off == 0) {
-        for (int v = threadIdx.x; v < nv; v += 256) store4(S + 4 * v, float4{0.f, 0.f, 0.f, 0.f});
+        for (int v = threadIdx.x; v < nv; v += blockDim.x) store4(S + 4 * v, float4{0.f, 0.f, 0.f, 0.f});
     }
     __syncthreads();  // S complete; every thread has read the old W
     if (threadIdx.x == 0) a.acc_w[seq] = (off == 0 ? 0.f : w_old) + (float)len;
     if (!last) return;
     float nn = 0.f;
-    for (int v = threadIdx.x; v < nv; v += 256) {
+    for (int v = threadIdx.x; v < nv; v += blockDim.x) {
         const float4 q = load4(S + 4 * v);
         nn += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
     }
     const float sc = 1.f / fmaxf(sqrtf(block_sum(nn, red)), 1e-12f);
     float *out = a.out_emb + (size_t)ci * a.d;
-    for (int v = threadIdx.x; v < nv; v += 256) {
+    for (int v = threadIdx.x; v < nv; v += blockDim.x) {
         const float4 q = load4(S + 4 * v);
         store4(out + 4 * v, float4{q.x * sc, q.y * sc, q.z * sc, q.w * sc});
     }
@@ -572,14 +572,274 @@ __global__ __launch_bounds__(256) void pool_rows_kernel(PoolArgs a) {
     pool_rows_block(a, blockIdx.x, red);
 }
 
-// With no head that needs every embedding row's norm, the final norm of the rows that get
-// logits and the single-row pooler are independent: one launch, blocks [0, n_lm) normalise the
-// LM rows, the following n_chunks blocks pool one chunk each.
+// ---- d <= 8192: the final norm and the pooler in one launch, plus two for chunks of several slices.
+// Blocks of two 256-thread groups: [0, ceil(n_lm / 2)) norm two LM rows each; then max_slices blocks
+// per chunk.  A mean, weighted-mean or buffered chunk is cut into slices of kPoolRows rows: the block
+// norms its rows (a group one row at a time, the next row and its pending slabs in flight) and sums
+// them in registers, so the rows are read once and never written back.  A chunk of one slice is
+// finished here, longer ones leave partial sums that pool_sum_slices adds.
+// Single-row heads take their row in slice 0's block.  Norm, row pooler, accumulation and finish as
+// launches of their own took 62 us on three 512-row chunks, 51 us on 1024 rows of short queries; these
+// take 25 and 31 us.
+constexpr int kPoolRows = kPoolSliceRows;
+
+// x row and its slabs, not yet added
+template <int RV>
+struct RawRow {
+    float4 x[RV], p[kMaxPend][RV];
+    __device__ __forceinline__ void load(const float *xrow, const float *pend, size_t stride, int npend, int t, int nv) {
+#pragma unroll
+        for (int i = 0; i < RV; ++i)
+            if (t + i * 256 < nv) x[i] = load4(xrow + 4 * (t + i * 256));
+#pragma unroll
+        for (int sp = 0; sp < kMaxPend; ++sp)
+            if (sp < npend) {
+#pragma unroll
+                for (int i = 0; i < RV; ++i)
+                    if (t + i * 256 < nv) p[sp][i] = load4(pend + sp * stride + 4 * (t + i * 256));
+            }
+    }
+    __device__ __forceinline__ void sum(float4 (&v)[RV], int npend) const {
+#pragma unroll
+        for (int i = 0; i < RV; ++i) v[i] = x[i];
+#pragma unroll
+        for (int sp = 0; sp < kMaxPend; ++sp)
+            if (sp < npend) {
+#pragma unroll
+                for (int i = 0; i < RV; ++i)
+                    v[i] = float4{v[i].x + p[sp][i].x, v[i].y + p[sp][i].y, v[i].z + p[sp][i].z, v[i].w + p[sp][i].w};
+            }
+    }
+};
+
+template <int RV>
+__device__ __forceinline__ float sum_squares(const float4 (&v)[RV], int t, int nv) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < RV; ++i)
+        if (t + i * 256 < nv) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+    return ss;
+}
+
+// out_emb of a final chunk from this thread's columns v0 + i * step of S: v / max(||v||, 1e-12)
+template <int NV>
+__device__ void finish_chunk(const PoolArgs &a, int ci, const float4 (&S)[NV], bool mine, int v0, int step, float W, float *red) {
+    const int32_t *ch = a.chunks + kChunkInts * ci;
+    const int flags = ch[3], nv = a.d / 4;
+    if (!(flags & ORTHRUS_CHUNK_LAST)) return;
+    const float div = ((flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK) == ORTHRUS_POOL_MEAN ? W : 1.f;
+    float4 v[NV];
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        if (!mine || v0 + i * step >= nv) continue;
+        v[i] = float4{S[i].x / div, S[i].y / div, S[i].z / div, S[i].w / div};
+        ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+    }
+    const float inv = 1.f / fmaxf(sqrtf(block_sum(ss, red)), 1e-12f);
+    float *out = a.out_emb + (size_t)ci * a.d;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = v0 + i * step;
+        if (mine && c < nv) store4(out + 4 * c, float4{v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv});
+    }
+}
+
+// S of Eq. (1) plus the gained total of four columns
+__device__ __forceinline__ float4 add_gained(float4 S, float4 tot, float4 g) {
+    return float4{S.x + tot.x * g.x, S.y + tot.y * g.y, S.z + tot.z * g.z, S.w + tot.w * g.w};
+}
+
+// the partial sums of chunk `ch`'s slices: disjoint per chunk, because a chunk of several slices has at
+// most len / 4 of them, and at most Te / 4 rows of d floats in all
+__device__ __forceinline__ float *slice_row(const PoolArgs &a, const int32_t *ch, int sl) {
+    return a.part + (size_t)(ch[4] / 4 + sl) * a.d;
+}
+
 template <typename T, int RV>
-__global__ __launch_bounds__(256) void final_and_pool_rows_kernel(PoolArgs a) {
-    __shared__ float red[4];
-    if ((int)blockIdx.x < a.n_lm) final_row_block<T, RV>(a, blockIdx.x, red);
-    else pool_rows_block(a, (int)blockIdx.x - a.n_lm, red);
+__global__ __launch_bounds__(512) void final_pool_kernel(PoolArgs a) {
+    __shared__ float red[8], rowred[2][2][4];
+    __shared__ float4 other[RV * 256];
+    const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+    const int lane = threadIdx.x & 63, gwave = (threadIdx.x >> 6) & 3, nv = a.d / 4;
+    // 1 / rms of the row in v; called by both groups together, alternating `par`
+    auto row_scale = [&](const float4 (&v)[RV], int par) {
+        const float ws = wave_sum(sum_squares<RV>(v, t, nv));
+        if (lane == 0) rowred[par][grp][gwave] = ws;
+        __syncthreads();
+        const float *r = rowred[par][grp];
+        return rsqrtf((r[0] + r[1] + r[2] + r[3]) / (float)a.d + a.eps);
+    };
+    RawRow<RV> raw;
+    float4 v[RV];
+    const int lm_blocks = (a.n_lm + 1) / 2;
+    if ((int)blockIdx.x < lm_blocks) {
+        const int lm = 2 * blockIdx.x + grp, r = a.lm_rows[min(lm, a.n_lm - 1)];
+        raw.load(a.x + (size_t)r * a.d, a.pend + (size_t)r * a.d, a.pend_stride, a.npend, t, nv);
+        raw.sum(v, a.npend);
+        const float inv = row_scale(v, 0);
+        if (lm >= a.n_lm) return;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const int c = t + i * 256;
+            if (c >= nv) continue;
+            const float4 g = load4(a.gen_gain + 4 * c);
+            store4((T *)a.act + (size_t)lm * a.d + 4 * c, float4{v[i].x * inv * g.x, v[i].y * inv * g.y, v[i].z * inv * g.z, v[i].w * inv * g.w});
+        }
+        return;
+    }
+    const int ci = (blockIdx.x - lm_blocks) / a.max_slices, sl = (blockIdx.x - lm_blocks) % a.max_slices;
+    const int32_t *ch = a.chunks + kChunkInts * ci;
+    const int seq = ch[0], off = ch[1], len = ch[2], flags = ch[3], t0 = ch[4];
+    const int pool = (flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
+    const bool sums = pool == ORTHRUS_POOL_MEAN || pool == ORTHRUS_POOL_WMEAN;
+    if (!sums && pool != ORTHRUS_POOL_BUFFER) {
+        if (sl == 0) pool_rows_block(a, ci, red);
+        return;
+    }
+    const int first = sl * kPoolRows, n = min(kPoolRows, len - first);
+    if (n <= 0) return;
+    const float w_old = a.acc_w[seq];
+    const bool ok = off == 0 || w_old == (float)off;
+    if (sums && !ok) {
+        if (sl == 0 && threadIdx.x == 0) flag_error(a.err, ORTHRUS_DEVERR_ACC);
+        return;
+    }
+    float4 acc[RV];
+#pragma unroll
+    for (int i = 0; i < RV; ++i) acc[i] = float4{0.f, 0.f, 0.f, 0.f};
+    // group g takes rows g, g + 2, ...; a row past the slice repeats its last one and is not added
+    auto row_of = [&](int k) { return t0 + first + min(2 * k + grp, n - 1); };
+    auto load_row = [&](int k) {
+        const size_t r = (size_t)row_of(k) * a.d;
+        raw.load(a.x + r, a.pend + r, a.pend_stride, a.npend, t, nv);
+    };
+    constexpr bool kPrefetch = RV <= 4;     // registers for two rows
+    if (kPrefetch) load_row(0);
+    const int iters = (n + 1) / 2;
+    for (int k = 0; k < iters; ++k) {
+        if (!kPrefetch) load_row(k);
+        raw.sum(v, a.npend);
+        if (kPrefetch && k + 1 < iters) load_row(k + 1);
+        const float inv = row_scale(v, k & 1);
+        if (2 * k + grp >= n) continue;
+        const int r = row_of(k);
+        const int hr = a.hid_rows ? a.hid_rows[r] : -1;
+        const float f = pool == ORTHRUS_POOL_WMEAN ? inv * a.weights[r] : inv;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            acc[i] = float4{acc[i].x + v[i].x * f, acc[i].y + v[i].y * f, acc[i].z + v[i].z * f, acc[i].w + v[i].w * f};
+            const int c = t + i * 256;
+            if (hr >= 0 && c < nv) {
+                const float4 g = load4(a.gain + 4 * c);
+                store4(a.hidden + (size_t)hr * a.d + 4 * c, float4{v[i].x * inv * g.x, v[i].y * inv * g.y, v[i].z * inv * g.z, v[i].w * inv * g.w});
+            }
+        }
+    }
+    if (!sums) return;      // buffered rows: written; pool_finish_slices counts them
+    if (grp == 1) {
+#pragma unroll
+        for (int i = 0; i < RV; ++i) other[i * 256 + t] = acc[i];
+    }
+    __syncthreads();        // every thread has read the old W by now
+    if (grp == 0) {
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const float4 o = other[i * 256 + t];
+            acc[i] = float4{acc[i].x + o.x, acc[i].y + o.y, acc[i].z + o.z, acc[i].w + o.w};
+        }
+    }
+    if (len <= kPoolRows) {
+        const float W = (off == 0 ? 0.f : w_old) + (float)len;
+        if (threadIdx.x == 0) a.acc_w[seq] = W;
+#pragma unroll
+        for (int i = 0; i < RV; ++i) {
+            const int c = t + i * 256;
+            if (grp == 1 || c >= nv) continue;
+            float *S = a.acc_sum + (size_t)seq * a.d + 4 * c;
+            acc[i] = add_gained(off == 0 ? float4{0.f, 0.f, 0.f, 0.f} : load4(S), acc[i], load4(a.gain + 4 * c));
+            store4(S, acc[i]);
+        }
+        finish_chunk<RV>(a, ci, acc, grp == 0, t, 256, W, red);
+        return;
+    }
+    if (grp == 0) {
+        float *dst = slice_row(a, ch, sl);
+#pragma unroll
+        for (int i = 0; i < RV; ++i)
+            if (t + i * 256 < nv) store4(dst + 4 * (t + i * 256), acc[i]);
+    }
+}
+
+// S of the mean and weighted-mean chunks of several slices.  Grid (chunks, 64-float4 columns), sixteen
+// waves: wave w adds slices w, w + 16, ..., the waves' sums meet in LDS in wave order.  A thread that
+// walked all slices of its column waited on them 16 at a time (64 slices 22 us, this 4.7).
+constexpr int kSliceWaves = 16;
+__global__ __launch_bounds__(64 * kSliceWaves) void pool_sum_slices(PoolArgs a) {
+    __shared__ float4 part[kSliceWaves][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ci = blockIdx.x, c = blockIdx.y * 64 + lane, nv = a.d / 4;
+    const int32_t *ch = a.chunks + kChunkInts * ci;
+    const int seq = ch[0], off = ch[1], len = ch[2], flags = ch[3];
+    const int pool = (flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
+    if ((pool != ORTHRUS_POOL_MEAN && pool != ORTHRUS_POOL_WMEAN) || len <= kPoolRows) return;
+    const int slices = (len + kPoolRows - 1) / kPoolRows;
+    const float *src = slice_row(a, ch, 0) + 4 * min(c, nv - 1);
+    float *S = a.acc_sum + (size_t)seq * a.d + 4 * min(c, nv - 1);
+    const float w_old = a.acc_w[seq];
+    float4 g{}, old{0.f, 0.f, 0.f, 0.f};
+    if (wave == 0) {
+        g = load4(a.gain + 4 * min(c, nv - 1));
+        if (off != 0) old = load4(S);
+    }
+    float4 tot{0.f, 0.f, 0.f, 0.f};
+    constexpr int kAhead = 4;
+    for (int sl = wave; sl < slices; sl += kAhead * kSliceWaves) {
+        float4 p[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) p[k] = load4(src + (size_t)min(sl + k * kSliceWaves, slices - 1) * a.d);
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (sl + k * kSliceWaves < slices) tot = float4{tot.x + p[k].x, tot.y + p[k].y, tot.z + p[k].z, tot.w + p[k].w};
+    }
+    part[wave][lane] = tot;
+    __syncthreads();
+    if (wave != 0 || c >= nv || !(off == 0 || w_old == (float)off)) return;
+#pragma unroll
+    for (int w = 1; w < kSliceWaves; ++w) {
+        const float4 o = part[w][lane];
+        tot = float4{tot.x + o.x, tot.y + o.y, tot.z + o.z, tot.w + o.w};
+    }
+    store4(S, add_gained(old, tot, g));
+}
+
+// then their token count and embedding, one block a chunk; buffered chunks: the token count
+constexpr int kFinishThreads = 1024;
+__global__ __launch_bounds__(kFinishThreads) void pool_finish_slices(PoolArgs a) {
+    __shared__ float red[kFinishThreads / 64];
+    constexpr int NV = 2;                     // d <= 8192
+    const int ci = blockIdx.x, nv = a.d / 4;
+    const int32_t *ch = a.chunks + kChunkInts * ci;
+    const int seq = ch[0], off = ch[1], len = ch[2], flags = ch[3];
+    const int pool = (flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
+    const bool sums = (pool == ORTHRUS_POOL_MEAN || pool == ORTHRUS_POOL_WMEAN) && len > kPoolRows;
+    if (!sums && pool != ORTHRUS_POOL_BUFFER) return;
+    const float w_old = a.acc_w[seq];
+    float4 S[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = threadIdx.x + i * kFinishThreads;
+        if (sums && (flags & ORTHRUS_CHUNK_LAST) && c < nv) S[i] = load4(a.acc_sum + (size_t)seq * a.d + 4 * c);
+    }
+    const bool ok = off == 0 || w_old == (float)off;
+    __syncthreads();                          // every thread has read the old W
+    if (!ok) {
+        if (!sums && threadIdx.x == 0) flag_error(a.err, ORTHRUS_DEVERR_ACC);
+        return;
+    }
+    const float W = (off == 0 ? 0.f : w_old) + (float)len;
+    if (threadIdx.x == 0) a.acc_w[seq] = W;
+    if (sums) finish_chunk<NV>(a, ci, S, true, threadIdx.x, kFinishThreads, W, red);
 }
 
 // ------------------------------------------------------------------------- greedy sampler
@@ -678,15 +938,22 @@ hipError_t launch_final_rows(int dtype, const PoolArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_final_and_pool(int dtype, const PoolArgs &a, hipStream_t s) {
-    if (a.n_emb_rows != 0) return hipErrorInvalidValue;
-    if (a.npend < 0 || a.npend > kMaxPend) return hipErrorInvalidValue;
-    const int blocks = a.n_lm + a.n_chunks;
+bool final_pool_takes(int d) { return d <= 8192; }
+
+hipError_t launch_final_pool(int dtype, const PoolArgs &a, bool slices, hipStream_t s) {
+    if (!final_pool_takes(a.d) || a.npend < 0 || a.npend > kMaxPend || a.max_len < 0) return hipErrorInvalidValue;
+    PoolArgs q = a;
+    q.max_slices = std::max(1, (a.max_len + kPoolRows - 1) / kPoolRows);
+    const long blocks = (a.n_lm + 1) / 2 + (long)a.n_chunks * q.max_slices;
     if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const bool rv4 = a.d <= 4096;
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, a); };
-    if (dtype == 1) rv4 ? go(final_and_pool_rows_kernel<bf16, 4>) : go(final_and_pool_rows_kernel<bf16, 8>);
-    else rv4 ? go(final_and_pool_rows_kernel<float, 4>) : go(final_and_pool_rows_kernel<float, 8>);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(512), 0, s, q); };
+    if (dtype == 1) rv4 ? go(final_pool_kernel<bf16, 4>) : go(final_pool_kernel<bf16, 8>);
+    else rv4 ? go(final_pool_kernel<float, 4>) : go(final_pool_kernel<float, 8>);
+    if (a.max_len > kPoolRows)
+        hipLaunchKernelGGL(pool_sum_slices, dim3(a.n_chunks, (a.d / 4 + 63) / 64), dim3(64 * kSliceWaves), 0, s, q);
+    if (slices) hipLaunchKernelGGL(pool_finish_slices, dim3(a.n_chunks), dim3(kFinishThreads), 0, s, q);
     return hipGetLastError();
 }
 

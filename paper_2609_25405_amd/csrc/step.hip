@@ -799,9 +799,18 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     pa.hidden = batch->hidden;
     pa.n_emb_rows = any_rows ? Te : 0;
     pa.n_lm = p.n_lm;
-    if (!any_rows && p.n_chunks > 0 && p.n_lm > 0) {
-        // independent work: LM rows' final norm and the single-row pooler in one launch
-        RUN("final_norm_pool", launch_final_and_pool(dt, pa, s));
+    if (final_pool_takes(d)) {
+        // slices' sums go behind the LM rows in act: Te / 4 rows of d floats, and the Te rows the
+        // embedding chunks leave free there hold at least twice that
+        pa.part = (float *)(act + (size_t)p.n_lm * d * es);
+        for (int i = 0; i < p.n_chunks; ++i) {
+            const int pool = (batch->chunks[i].flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
+            if (pool == ORTHRUS_POOL_MEAN || pool == ORTHRUS_POOL_WMEAN || pool == ORTHRUS_POOL_BUFFER)
+                pa.max_len = std::max(pa.max_len, batch->chunks[i].len);
+        }
+        if (p.n_lm + p.n_chunks > 0)
+            RUN(p.n_chunks > 0 ? "final_norm_pool" : "final_norm",
+                launch_final_pool(dt, pa, pa.max_len > kPoolSliceRows || p.any_buffer, s));
     } else {
         if (pa.n_emb_rows + pa.n_lm > 0) RUN("final_norm", launch_final_rows(dt, pa, s));
         // the embedding rows' pending slabs were added by the final norm when it covered them
