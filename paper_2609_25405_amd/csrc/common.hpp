@@ -84,10 +84,10 @@ struct GemmArgs {
     // B0 in the 64 x 64 blocked layout ([ceil(N/64)][K/64][64][64]; bf16 path, not SwiGLU):
     // one tile stage reads whole 8 KB runs instead of 128-byte pieces of 64 rows
     int b_blocked;
-    // 1: the launch runs concurrently with another stream's launches, so the workgroup time it
-    // takes from the shared CUs, not its own length, is what it costs; the bf16 dispatch then
-    // gives split-K projections of 129..256 rows the largest tiles, and larger ones tiles that
-    // leave registers and LDS to that stream's small kernels
+    // The launch's company.  0: none that matters; 1, 2: another stream's launches run beside it, so
+    // it leaves registers and LDS to that stream's small kernels: with 1 (every group of at most 896
+    // rows) on the large kernel's light tile shapes, with 2 on the 256-row tiles of gemm.hip,
+    // whose workgroup time per flop is the least of those that leave room
     int wide;
 };
 hipError_t launch_gemm(int dtype, int epilogue, const GemmArgs &a, hipStream_t s);
@@ -96,7 +96,7 @@ hipError_t launch_block_weights(const void *src, void *dst, int rows, int cols, 
 // split-K factor (<= max_splits; each split a run of whole 64-deep stages, the stages dealt as
 // evenly as the count allows) for a bf16 residual-add projection of this shape; launch_gemm
 // ignores a requested split count larger than K's number of stages
-int gemm_add_splits(int M, int N, int K, int max_splits, bool wide);
+int gemm_add_splits(int M, int N, int K, int max_splits, bool wide);  // wide: beside another stream's launches
 // the same for a QKV projection (1 or 2), whose rows or partial sums launch_rope_append reads
 int gemm_qkv_splits(int M, int N, int K, bool wide);
 

@@ -459,20 +459,22 @@ bool ring_split(int M, int N, int K, int splits) {
 //    rows: gate/up 93.5 / 169.7 / 246.9 -> 84.6 / 129.8 / 190.3 us, down 68.4 / 116.1 / 124.3 ->
 //    56.8 / 74.4 / 87.8, o 22.9 / 35.1 / 37.8 -> 18.9 / 25.4 / 33.0; 2048-wide layer, 370 rows:
 //    42.5, 26.7, 12.3 -> 31.6, 22.0, 10.3);
-//  - beside another stream's launches (GemmArgs::wide) the large kernel leaves no registers and no
-//    LDS for that stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against
-//    5.99 ms), and this file's tiles stay: split-K projections of 129..256 rows and of more than
+//  - beside another stream's launches the large kernel's 256-row tiles leave no registers and no LDS
+//    for that stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against 5.99 ms).
+//    Groups of at most 896 rows (GemmArgs::wide 1) take its light shapes (two models, 4 layers, 512 +
+//    256 rows 2.58 -> 2.47 ms, 256 + 64 rows 1.43 -> 1.39 against this file's tiles); beside larger
+//    groups (wide 2) this file's tiles stay: split-K projections of 129..256 rows and of more than
 //    896 on 256x256 (fewest workgroup-microseconds per flop; the other stream's launches fill the
-//    rest), gate/up above 256 rows on the 192x256, 256x256 or 128x128 tiles that need the fewest
-//    rounds or pad the rows least.
+//    rest; the light shapes take 6.75 instead of 5.99 ms), gate/up above 256 rows on the 192x256,
+//    256x256 or 128x128 tiles that need the fewest rounds or pad the rows least.
 template <int EPI>
 hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
-    const bool big = !a.wide && gemm_big_takes(a);
+    const bool big = gemm_big_takes(a) && a.wide < 2;
     if constexpr (EPI == EPI_SWIGLU) {
         if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (big) {
-            const BigPlan p = plan_big(a.M, a.N, a.K, true, 1);
+            const BigPlan p = plan_big(a.M, a.N, a.K, true, 1, a.wide);
             // (plan_big's estimate is for weights that several row tiles share; read once, from HBM, they
             // take a fifth longer: 160 / 256 rows of the 7B gate/up est. 57 / 65, measured 64 / 80 us)
             if (a.M > 256 || 1.2 * p.us < stream256_us(2 * a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
@@ -500,7 +502,7 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         if (EPI != EPI_ADD_F32 && a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 128) return run_bf16<128, 128, 4, 2, EPI>(a, s);
         if (big && !(split && ring_split(a.M, a.N, a.K, a.splits))) {
-            const BigPlan p = plan_big(a.M, a.N, a.K, false, split ? a.splits : 1);
+            const BigPlan p = plan_big(a.M, a.N, a.K, false, split ? a.splits : 1, a.wide);
             if (a.M > 256 || EPI == EPI_ADD_F32 || p.us < stream256_us(a.N, a.K)) return launch_gemm_big(EPI, a, p, s);
         }
         // stored rows of 129..256 (the LM head of up to 256 decode rows): one 256-row tile, the
@@ -522,14 +524,13 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
 //  - 64 < M <= 128: 4 (weight streaming wants many workgroups);
 //  - M > 128: 4 for the long runs of ring_split, else the factor whose cover of the output
 //    (plan_big) and slabs take least time;
-//  - beside another stream's launches (wide): 4 up to M = 640, then 2 (128x128 tiles), above 896
-//    (256x256 tiles, one workgroup per CU) the factor with the least (rounds of workgroups over
-//    256 CUs) x (stages per split), the smaller one on a tie.
+//  - M > 896 beside another stream's launches (256x256 tiles, one workgroup per CU): the factor with
+//    the least (rounds of workgroups over 256 CUs) x (stages per split), the smaller one on a tie.
 int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
     auto valid = [&](int s) { return s <= max_splits && K % BK == 0 && K / s >= 512; };
-    if (M > 128 && !wide) {
+    if (M > 128 && (!wide || M <= 896)) {
         if (valid(4) && ring_split(M, N, K, 4)) return 4;
-        return big_splits(M, N, K, max_splits);
+        return big_splits(M, N, K, max_splits, wide);
     }
     if (M > 896) {
         const int stages = K / BK;
@@ -544,7 +545,7 @@ int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
         return best;
     }
     if (M > 64) {
-        int s = M <= 640 ? 4 : 2;
+        int s = 4;
         while (s > 1 && !valid(s)) s /= 2;
         return s;
     }
@@ -562,11 +563,12 @@ int gemm_add_splits(int M, int N, int K, int max_splits, bool wide) {
 
 // Splits (1 or 2) of a QKV projection, whose fp32 rows or partial sums the rotation/append kernel
 // reads: two for up to 128 rows (whole-K tiles leave too few workgroups for the weights: 64 rows of
-// the 7B shape 42.6 -> 18.6 us, rotation included 25.5) and beside another stream's launches up to
-// 1280 rows, else as the covers' estimates say.
+// the 7B shape 42.6 -> 18.6 us, rotation included 25.5), else as the covers' estimates say.  Beside
+// another stream's launches one up to 896 rows (the shorter launch is worth less than the partial
+// sums' traffic: 256 + 64 rows 1.456 against 1.394 ms) and above 1280, two between.
 int gemm_qkv_splits(int M, int N, int K, bool wide) {
     if (K % (2 * BK) || K / 2 < 512) return 1;
-    if (M <= 128 || (wide && M <= 1280)) return 2;
+    if (M <= 128 || (wide && M > 896 && M <= 1280)) return 2;
     return wide ? 1 : big_splits(M, N, K, 2);
 }
 

@@ -353,11 +353,11 @@ double makespan(long n1, double c1, long n2, double c2) {
 double stage_us(int bm, int bn, int per_cu) { return 0.44 + 0.0155e-3 * bm * bn * per_cu; }
 constexpr double kTileUs = 4.0;
 
-struct Shape { int id, bm, bn, per_cu; };
+struct Shape { int id, bm, bn, per_cu; bool light; };
 // shapes that cover an output alone (ids as in launch_shape); per_cu: workgroups whose LDS and
-// registers fit one CU
-constexpr Shape kAlone[] = {{4, 192, 256, 1}, {5, 192, 192, 1}, {6, 192, 128, 1}, {7, 128, 256, 1},
-                            {8, 128, 128, 2}, {9, 64, 256, 1},  {10, 64, 128, 2}};
+// registers fit one CU; light: at most 120 registers and 112 KB
+constexpr Shape kAlone[] = {{4, 192, 256, 1, false}, {5, 192, 192, 1, false}, {6, 192, 128, 1, true}, {7, 128, 256, 1, false},
+                            {8, 128, 128, 2, true}, {9, 64, 256, 1, true},  {10, 64, 128, 2, true}};
 
 }  // namespace
 
@@ -366,7 +366,7 @@ constexpr Shape kAlone[] = {{4, 192, 256, 1}, {5, 192, 192, 1}, {6, 192, 128, 1}
 // smaller tiles, or (few rows, where a round of 256 x 256 tiles is never full) one smaller shape
 // covers everything.  544 rows of the 7B gate/up: 192x192 130 us, 256x256 154; down, K split
 // three ways: 128x128 74 us, 256x256 96.
-static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
+static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits, bool light) {
     const int C = swiglu ? 128 : 256, f = swiglu ? 2 : 1;
     const int mt = (M + 255) / 256, nt = (N + C - 1) / C;
     const double stages = (double)K / kBK / splits;
@@ -376,13 +376,13 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
     best.m_main = mt;
     best.n_main = nt;
     best.splits = splits;
-    best.us = makespan((long)mt * nt * splits, c256, 0, 0.0);
+    best.us = light ? 1e30 : makespan((long)mt * nt * splits, c256, 0, 0.0);
     auto offer = [&](const BigPlan &p) {
         if (p.us < best.us * 0.98) best = p;
     };
     // the last rows on 128- or 64-row tiles
     const int rem = M % 256;
-    if (M > 256 && rem > 0 && rem <= 128) {
+    if (!light && M > 256 && rem > 0 && rem <= 128) {
         const int bm = rem <= 64 ? 64 : 128;
         BigPlan p;
         p.shape = bm == 64 ? 11 : 1;
@@ -396,7 +396,7 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
         offer(p);
     }
     // columns past the first j column tiles on 192- or 128-wide tiles
-    for (int shape = 2; shape <= 3; ++shape) {
+    for (int shape = 2; shape <= 3 && !light; ++shape) {
         const int w = (shape == 2 ? 192 : 128) / f;
         for (int j = 0; j < nt; ++j) {
             BigPlan p;
@@ -412,6 +412,7 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
         }
     }
     for (const Shape &sh : kAlone) {
+        if (light && !sh.light) continue;
         BigPlan p;
         p.shape = sh.id;
         p.m_alt = (M + sh.bm - 1) / sh.bm;
@@ -427,23 +428,23 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits) {
 
 // The search takes a few microseconds; a layer asks for the same four covers as the one before it, so
 // each thread keeps the last ones it computed (a pure function of the sizes).
-BigPlan plan_big(int M, int N, int K, bool swiglu, int splits) {
-    struct Entry { int M = -1, N = 0, K = 0, sw = 0, splits = 0; BigPlan plan; };
+BigPlan plan_big(int M, int N, int K, bool swiglu, int splits, bool light) {
+    struct Entry { int M = -1, N = 0, K = 0, sw = 0, splits = 0, light = 0; BigPlan plan; };
     static thread_local Entry memo[64];
-    const unsigned h = (unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)(splits * 2 + swiglu) * 668265263u;
+    const unsigned h = (unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)(splits * 4 + swiglu * 2 + light) * 668265263u;
     Entry &e = memo[h >> 26];
-    if (e.M != M || e.N != N || e.K != K || e.sw != (int)swiglu || e.splits != splits)
-        e = Entry{M, N, K, (int)swiglu, splits, search_plan(M, N, K, swiglu, splits)};
+    if (e.M != M || e.N != N || e.K != K || e.sw != (int)swiglu || e.splits != splits || e.light != (int)light)
+        e = Entry{M, N, K, (int)swiglu, splits, (int)light, search_plan(M, N, K, swiglu, splits, light)};
     return e.plan;
 }
 
-int big_splits(int M, int N, int K, int max_splits) {
+int big_splits(int M, int N, int K, int max_splits, bool light) {
     int best = 1;
     double best_us = 0.0;
     for (int s = 1; s <= max_splits; ++s) {
         if (s > 1 && (K % kBK || K / s < 512)) continue;
         // the next row kernel reads every slab, at about 4 TB/s
-        const double us = plan_big(M, N, K, false, s).us + s * ((double)M * N * 4 / 4e6);
+        const double us = plan_big(M, N, K, false, s, light).us + s * ((double)M * N * 4 / 4e6);
         if (s == 1 || us < best_us) { best = s; best_us = us; }
     }
     return best;

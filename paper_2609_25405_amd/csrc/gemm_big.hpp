@@ -16,10 +16,11 @@ struct BigPlan {
     int add = 0;      // fp32 rows: add into the output (unsplit) instead of storing
     double us = 0;    // estimated length in microseconds
 };
-// the cover of [M][N] (swiglu: N gate and N up rows of weights) with the least estimated length
-BigPlan plan_big(int M, int N, int K, bool swiglu, int splits);
+// the cover of [M][N] (swiglu: N gate and N up rows of weights) with the least estimated length; light:
+// only of shapes that leave a CU's registers and LDS room for another stream's small kernels
+BigPlan plan_big(int M, int N, int K, bool swiglu, int splits, bool light = false);
 // the split-K factor (at least 512 deep) whose cover and slabs take least time
-int big_splits(int M, int N, int K, int max_splits);
+int big_splits(int M, int N, int K, int max_splits, bool light = false);
 // whether the kernel's addressing covers these operands (K % 64 == 0, rows of at most 8 MB)
 bool gemm_big_takes(const GemmArgs &a);
 // EPI_STORE_F32, EPI_ADD_F32 (with plan.splits > 1: slabs in a.partial) or EPI_SWIGLU

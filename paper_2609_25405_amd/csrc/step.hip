@@ -490,6 +490,20 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         }
         return launch_lora_shrink(dt, sh, g.st);
     };
+    int max_rows = 0;
+    for (int gi = 0; gi < n_groups; ++gi) max_rows = std::max(max_rows, groups[gi].r1 - groups[gi].r0);
+    // How a launch shares the chip with the other group's (GemmArgs::wide).  Where one group has at
+    // least five times the other's rows (and more than 896) its chain is the step's length, so its
+    // launches are sized as if alone (two models, 4 layers, 256 decode rows: 1792 query tokens 4.37 ->
+    // 3.98 ms, 1500 3.89 -> 3.72; at four times the rows the other chain is as long, and big launches
+    // that its small ones wait for cost 1 %: 1024 tokens, 8 layers 5.98 -> 6.04).
+    int min_rows = max_rows;
+    for (int gi = 0; gi < n_groups; ++gi) min_rows = std::min(min_rows, groups[gi].r1 - groups[gi].r0);
+    const bool lopsided = concurrent && max_rows > 896 && max_rows >= 5 * min_rows;
+    auto wide_of = [&](const Group &g) {
+        if (!concurrent || (lopsided && g.r1 - g.r0 == max_rows)) return 0;
+        return max_rows <= 896 ? 1 : 2;
+    };
     auto gemm = [&](int epi, const Group &g, const char *A, int lda, const void *B0, const void *B1,
                     void *out, int ldo, size_t out_es, int N, int K, const LoraGemm &lg) -> hipError_t {
         GemmArgs ga{};
@@ -504,15 +518,13 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ga.ldo = ldo;
         ga.splits = 1;
         ga.lora = lg;
-        ga.wide = concurrent;
+        ga.wide = wide_of(g);
         return launch_gemm(dt, epi, ga, g.st);
     };
     // residual-add projection into x; bf16: split K when the tile count is low and leave the
     // slabs for the next row-wise kernel.  `splits` is chosen once per projection for the largest
     // row group and used by every group, so the pending slab count is the same for all rows.
-    int max_rows = 0;
-    for (int gi = 0; gi < n_groups; ++gi) max_rows = std::max(max_rows, groups[gi].r1 - groups[gi].r0);
-    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits, concurrent) : 1; };
+    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits, concurrent && !lopsided) : 1; };
     auto add_proj = [&](const Group &g, const char *A, int lda, const void *B, int K, int splits,
                         const LoraGemm &lg) -> hipError_t {
         GemmArgs ga{};
@@ -528,7 +540,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ga.partial = slabs ? slabs + (size_t)g.r0 * d : nullptr;  // the group's rows of each slab
         ga.split_stride = slab_stride;
         ga.lora = lg;
-        ga.wide = concurrent;
+        ga.wide = wide_of(g);
         return launch_gemm(dt, EPI_ADD_F32, ga, g.st);
     };
 
@@ -662,7 +674,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ra.k_cache[1] = (char *)gen_kv->k_cache + l * g_stride;
         ra.v_cache[1] = (char *)gen_kv->v_cache + l * g_stride;
         const int qkv_splits = dt == ORTHRUS_BF16 && (size_t)kQkvSplits * T <= qkv_slab_rows(T)
-                                   ? gemm_qkv_splits(max_rows, qkvd, d, concurrent)
+                                   ? gemm_qkv_splits(max_rows, qkvd, d, concurrent && !lopsided)
                                    : 1;
         if (sk_qkv) {
             for (int gi = 0; gi < n_groups; ++gi) {
@@ -687,7 +699,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
                 ga.splits = qkv_splits;
                 ga.partial = qkv + (size_t)g.r0 * qkvd;
                 ga.split_stride = (size_t)T * qkvd;
-                ga.wide = concurrent;
+                ga.wide = wide_of(g);
                 if (lora_on(0, g)) RUNG(g, "lora_shrink", lora(0, l, g, act, d, d, ga.lora));
                 RUNG(g, "gemm_qkv", launch_gemm(dt, EPI_ADD_F32, ga, g.st));
             }
