@@ -41,7 +41,7 @@ PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 METRIC = "mixed-step throughput: embed tokens/s + decode tokens/s; %MFMA and %HBM peak"
 PROFILES = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_25405_amd", "csrc", f) for f in ("gemm.hip", "common.hpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_25405_amd", "csrc", f) for f in ("gemm.hip", "gemm_big.hip", "common.hpp")]
 DATA = "synthetic (seeded N(0,0.02) weights and N(0,1) bf16 caches drawn on the device, uniform token ids)"
 GEMMS = ("gemm_qkv", "gemm_qkv_rope", "gemm_o", "gemm_gate_up", "gemm_down", "lm_head")
 
@@ -104,8 +104,8 @@ def launch_work(cfg, batch, two_models: bool):
     their weights, input rows and output rows (residual-add projections read and write the fp32
     residual rows once); attention 4 hd nq flops per (query, visible key) pair of chunk rows and
     decode rows, over every visible key's K and V once per KV head plus q and o; norms and the
-    final norm / pooler over their rows.  Split-K slabs, attention partials and the fp32 rows of
-    the unfused rotation path are implementation traffic: rope_append and attn_combine carry no
+    final norm / pooler over their rows.  Split-K slabs, attention partials and the fp32 QKV rows
+    that the rotation kernel reads are implementation traffic: rope_append and attn_combine carry no
     algorithmic work (their work is counted in gemm_qkv and attention)."""
     d, F, V, L = cfg.d_model, cfg.d_ff, cfg.vocab, cfg.n_layers
     qd, kvd, qkv = cfg.q_dim, cfg.kv_dim, cfg.qkv_dim

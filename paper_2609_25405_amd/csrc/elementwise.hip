@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(NormArgs a) {
             load_row_pend<RV>(xv, xrow, a.pend + (size_t)r * a.d, a.pend_stride, a.npend, nv);
         }
         if (GATHER && a.cs && (int)threadIdx.x < a.hd / 2) {
-            // rotation table of this token for the QKV epilogue (angle evaluated in double)
+            // rotation table of this token for the rotation kernels (angle evaluated in double)
             const double inv_freq = pow((double)a.rope_base, -2.0 * (double)threadIdx.x / (double)a.hd);
             double sv, cv;
             sincos((double)a.pos[r] * inv_freq, &sv, &cv);
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(NormArgs a) {
         return;
     }
     if (GATHER && a.cs && (int)threadIdx.x < a.hd / 2) {
-        // rotation table of this token for the QKV epilogue (angle evaluated in double)
+        // rotation table of this token for the rotation kernels (angle evaluated in double)
         const double inv_freq = pow((double)a.rope_base, -2.0 * (double)threadIdx.x / (double)a.hd);
         double sv, cv;
         sincos((double)a.pos[r] * inv_freq, &sv, &cv);
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(NormArgs a) {
 template <typename T>
 // One token per blockIdx.x; its work items (rotation quads of the q and k heads, then value
 // quads) are dealt over gridDim.y blocks.  Angles come from the per-token table when the step
-// built one (the same values the fused GEMM epilogue uses), else in double here.
+// built one, else in double here.
 __global__ __launch_bounds__(256) void rope_append_kernel(RopeArgs a) {
     __shared__ __attribute__((aligned(16))) float cs[64], sn[64];
     const int t = blockIdx.x;

@@ -1,7 +1,8 @@
 // Dense projections of the step: C[M][N] = A[M][K] * W[N][K]^T over the concatenated token
-// batch (QKV, attention output, gate/up, down, LM head), with fused epilogues.
+// batch (QKV, attention output, gate/up, down, LM head), with fused epilogues, and the choice of
+// kernel per shape (dispatch_bf16; above 128 rows mostly gemm_big.hip).
 //
-// bf16 path: CDNA4 MFMA v_mfma_f32_32x32x16_bf16, WM x WN wave64s per workgroup, K staged 64
+// bf16 path, kernel of this file: CDNA4 MFMA v_mfma_f32_32x32x16_bf16, WM x WN wave64s per workgroup, K staged 64
 // elements at a time through two LDS buffers filled by direct global->LDS copies
 // (global_load_lds_dwordx4, no register staging), so each K stage costs one barrier.  LDS rows
 // are 128 B; 16-byte chunks are XOR-swizzled by row so the per-lane 16-byte operand reads of
