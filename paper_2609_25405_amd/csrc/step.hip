@@ -496,12 +496,15 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     // least five times the other's rows (and more than 896) its chain is the step's length, so its
     // launches are sized as if alone (two models, 4 layers, 256 decode rows: 1792 query tokens 4.37 ->
     // 3.98 ms, 1500 3.89 -> 3.72; at four times the rows the other chain is as long, and big launches
-    // that its small ones wait for cost 1 %: 1024 tokens, 8 layers 5.98 -> 6.04).
+    // that its small ones wait for cost 1 %: 1024 tokens, 8 layers 5.98 -> 6.04).  K splits and kernels
+    // follow the groups' sizes alone, also where no_alloc runs the groups one after the other: a
+    // step's sums are then the same on either entry point.
     int min_rows = max_rows;
     for (int gi = 0; gi < n_groups; ++gi) min_rows = std::min(min_rows, groups[gi].r1 - groups[gi].r0);
-    const bool lopsided = concurrent && max_rows > 896 && max_rows >= 5 * min_rows;
+    const bool lopsided = n_groups == 2 && max_rows > 896 && max_rows >= 5 * min_rows;
+    const bool shared_chip = n_groups == 2 && !lopsided;
     auto wide_of = [&](const Group &g) {
-        if (!concurrent || (lopsided && g.r1 - g.r0 == max_rows)) return 0;
+        if (n_groups == 1 || (lopsided && g.r1 - g.r0 == max_rows)) return 0;
         return max_rows <= 896 ? 1 : 2;
     };
     auto gemm = [&](int epi, const Group &g, const char *A, int lda, const void *B0, const void *B1,
@@ -524,7 +527,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
     // residual-add projection into x; bf16: split K when the tile count is low and leave the
     // slabs for the next row-wise kernel.  `splits` is chosen once per projection for the largest
     // row group and used by every group, so the pending slab count is the same for all rows.
-    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits, concurrent && !lopsided) : 1; };
+    auto add_splits = [&](int K) { return slabs ? gemm_add_splits(max_rows, d, K, kMaxSplits, shared_chip) : 1; };
     auto add_proj = [&](const Group &g, const char *A, int lda, const void *B, int K, int splits,
                         const LoraGemm &lg) -> hipError_t {
         GemmArgs ga{};
@@ -674,7 +677,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         ra.k_cache[1] = (char *)gen_kv->k_cache + l * g_stride;
         ra.v_cache[1] = (char *)gen_kv->v_cache + l * g_stride;
         const int qkv_splits = dt == ORTHRUS_BF16 && (size_t)kQkvSplits * T <= qkv_slab_rows(T)
-                                   ? gemm_qkv_splits(max_rows, qkvd, d, concurrent && !lopsided)
+                                   ? gemm_qkv_splits(max_rows, qkvd, d, shared_chip)
                                    : 1;
         if (sk_qkv) {
             for (int gi = 0; gi < n_groups; ++gi) {

@@ -109,9 +109,8 @@ def test_noalloc_step_equals_workspace_step_two_models():
 
 
 def test_noalloc_two_models_wide_generator_group():
-    """A generator group of 129..256 decode rows beside the embedding rows: the two-stream step gives
-    that group's split-K projections 256x256 tiles, the allocation-free one-stream step 128x128;
-    each output element sums the same K stages in the same order either way, so bitwise equal."""
+    """A generator group of 129..256 decode rows beside the embedding rows (projections too shallow
+    for a K split of QKV)."""
     cfg = _cfg()
     dm_e = R.DeviceModel(cfg, make_weights(cfg, 2305, model_tag=1, qk_std=0.06))
     dm_g = R.DeviceModel(cfg, make_weights(cfg, 2305, model_tag=2, qk_std=0.06))
@@ -129,6 +128,29 @@ def test_noalloc_two_models_wide_generator_group():
     small = Batch([EmbChunk(1, 120, 30, True, "cls")], [DecodeRow(s, ctx[s] + 1) for s in range(150)],
                   draw_tokens(2305, 4, 30 + 150, 512))
     run_both(dm_e, dm_g, pe, pg, [big, small], 4)
+
+
+@pytest.mark.parametrize("d,emb,n_g", [(1024, 300, 200), (2048, 520, 40), (1024, 1000, 300), (1024, 1000, 100)],
+                         ids=["split-qkv", "split-o", "large", "lopsided"])
+def test_noalloc_two_models_splits(d, emb, n_g):
+    """Two models at widths whose projections split K: K splits, tile shapes and kernels follow the sizes
+    of the two row groups, never whether the groups run on one stream or on two.  Groups of at most
+    896 rows, a larger one, and one five times the other."""
+    cfg = ModelConfig(n_layers=2, d_model=d, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=2048, vocab=256, dtype="bf16")
+    dm_e = R.DeviceModel(cfg, make_weights(cfg, 2306, model_tag=1, qk_std=0.06))
+    dm_g = R.DeviceModel(cfg, make_weights(cfg, 2306, model_tag=2, qk_std=0.06))
+    lens = [200] * (emb // 200) + [emb % 200] * (emb % 200 > 0)
+    pe = PagedKV(cfg, len(lens) * 13, len(lens), 13, 1)
+    pg = PagedKV(cfg, n_g * 4, n_g, 4, 2)
+    for s, n in enumerate(lens):
+        pe.reserve(s, n)
+    ctx = [5 + (11 * s) % 50 for s in range(n_g)]
+    for s, c in enumerate(ctx):
+        pg.fill_random(s, c, 5)
+        pg.reserve(s, c + 1)
+    batch = Batch([EmbChunk(s, 0, n, True, "mean") for s, n in enumerate(lens)], [DecodeRow(s, c) for s, c in enumerate(ctx)],
+                  draw_tokens(2306, 3, emb + n_g, cfg.vocab))
+    run_both(dm_e, dm_g, pe, pg, [batch], len(lens))
 
 
 def test_noalloc_error_bits_and_capacity():
