@@ -464,6 +464,40 @@ struct PrefillStageF32 {
     static __device__ __forceinline__ int vchunk(int d, int c) { return c ^ ((d >> 2) & 3); }
 };
 
+// One query row a lane pair (half: which half of the dims), key after key, so that nothing a row does not see
+// enters its sums: a wave's rows where a value beside its diagonal is not finite.  (Bad pages were flagged.)
+template <int HD>
+__device__ void rows_key_by_key(const PoolView &pv, const int32_t *bt, int g, size_t page_elems, const float *qp, int qpos,
+                                float scale, int half, float *op) {
+    constexpr int N = HD / 2;
+    float q[N], acc[N], m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int d = 0; d < N; ++d) {
+        q[d] = qp[half * N + d] * scale;
+        acc[d] = 0.f;
+    }
+    for (int kp = 0; kp <= qpos; ++kp) {
+        const int page = bt[kp / kPage];
+        if (page < 0 || page >= pv.n_pages) continue;
+        const float *kr = (const float *)pv.k + page * page_elems + ((size_t)g * kPage + kp % kPage) * HD + half * N;
+        const float *vr = (const float *)pv.v + page * page_elems + ((size_t)g * HD + half * N) * kPage + kp % kPage;
+        float s = 0.f;
+#pragma unroll
+        for (int d = 0; d < N; ++d) s = fmaf(q[d], kr[d], s);
+        s += __shfl_xor(s, 32, 64);
+        const float mn = fmaxf(m, s);
+        const float alpha = exp2f(m - mn), p = exp2f(s - mn);
+        l = l * alpha + p;
+#pragma unroll
+        for (int d = 0; d < N; ++d) acc[d] = fmaf(p, vr[d * kPage], acc[d] * alpha);
+        m = mn;
+    }
+    if (!op) return;
+    const float inv = l > 0.f ? 1.f / l : 0.f;      // (not a number where a key the row sees is not)
+#pragma unroll
+    for (int d = 0; d < N; ++d) op[half * N + d] = acc[d] * inv;
+}
+
 template <int HD, int G>
 __device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it, char *smem) {
     using St = PrefillStageF32<HD>;
@@ -555,6 +589,7 @@ __device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it, char *sme
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[d][e] = 0.f;
     float m = -INFINITY, l = 0.f;
+    bool odd = false;
     const float scale = kLog2e / sqrtf((float)HD);
     const int wave_first = off + qb + sb * 32;
 
@@ -596,13 +631,27 @@ __device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it, char *sme
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[d][e] *= alpha;
         }
+        auto value = [&](int q4, int d) {
+            const int dim = d * 32 + col;
+            return *(const f32x4 *)(vl + (q4 >> 1) * St::VPAGE + dim * 64 + St::vchunk(dim, (q4 & 1) * 2 + half) * 16);
+        };
+        // in a block that some row sees only in part: a masked key's weight is zero, and zero times a
+        // value that is not finite is NaN
+        if (kb * St::KEYS + St::KEYS - 1 > wave_first) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                for (int d = 0; d < DB; ++d) {
+                    const f32x4 vf = value(q4, d);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd |= !__builtin_isfinite(vf[e]);
+                }
+        }
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
             for (int d = 0; d < DB; ++d) {
-                const int dim = d * 32 + col;
-                const f32x4 vf = *(const f32x4 *)(vl + (q4 >> 1) * St::VPAGE + dim * 64 +
-                                                  St::vchunk(dim, (q4 & 1) * 2 + half) * 16);
+                const f32x4 vf = value(q4, d);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     acc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[e], p[q4 * 4 + e], acc[d], 0, 0, 0);
@@ -630,9 +679,13 @@ __device__ void prefill_item_f32(const AttnArgs &a, const int32_t *it, char *sme
         pg_cur[0] = pg_nxt[0];
         pg_cur[1] = pg_nxt[1];
     }
+    float *op = (float *)a.o + ((size_t)tok * a.nq + h) * HD;
+    if (__ballot(odd) != 0) {
+        rows_key_by_key<HD>(pv, bt, g, page_bytes / 4, qp, qpos, scale, half, col < rows ? op : nullptr);
+        return;
+    }
     if (col >= rows) return;
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    float *op = (float *)a.o + ((size_t)tok * a.nq + h) * HD;
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll

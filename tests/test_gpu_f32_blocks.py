@@ -2,11 +2,13 @@
 oracle: chunks that end on, before and after a 32-key block and a 32-row wave, a resumed chunk whose
 keys pass the staged window of 512 pages, decode rows on both sides of the 64-key pass and of
 the 256-key split, projections whose eight K slices hold unequal runs (K = 320) or fewer than one
-round (K = 64), and caches whose base is only element-aligned."""
+round (K = 64), and caches whose base is only element-aligned; a token whose keys and values are not
+numbers, which no earlier row of its chunk may see."""
 import pytest
 import torch
 
 from tests.parity import Pair
+from paper_2609_25405_amd import runtime as R
 from workload import Batch, DecodeRow, EmbChunk, ModelConfig, PagedKV, draw_tokens, make_weights
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +54,35 @@ def test_blocks(cfg, misaligned):
             setattr(pair.dkv_e, name, room[1:].view(t.shape))
     pair.workspace(batch.n_tokens, len(spans), len(ctx), 301)
     pair.step(batch)
+
+
+@pytest.mark.parametrize("nq,nkv,hd", [(4, 4, 64), (4, 2, 128), (4, 1, 64)])
+@pytest.mark.parametrize("offset,n,bad", [(0, 70, 1), (0, 70, 31), (13, 100, 57), (40, 33, 32)])
+def test_rows_before_a_token_that_is_not_a_number(nq, nkv, hd, offset, n, bad):
+    """Rows before the bad token equal a run in which its row of the table is a number (to the order of
+    the fp32 sums: 1e-5, as sums of at most 256 products differ): a masked key's weight is zero, and zero
+    times its value must not enter the sum.  It and the rows after it are not numbers."""
+    cfg = ModelConfig(n_layers=2, d_model=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ff=128, vocab=32, dtype="f32")
+    ids = draw_tokens(9, 0, n, 31)
+    ids[bad] = 31
+    W = make_weights(cfg, 22)
+    hidden = []
+    for value in (0.5, float("nan")):
+        W["tok_emb"][31] = value
+        kv = PagedKV(cfg, 40, 1, 20, 4)
+        if offset:
+            kv.fill_random(0, offset, 5)
+        kv.reserve(0, offset + n)
+        dm, dkv = R.DeviceModel(cfg, W), R.DeviceKV.from_paged(kv)
+        ws = R.Workspace(dm, dm, n, 1, 0, 1)
+        S, Wc = torch.zeros((1, 256), device="cuda"), torch.full((1,), float(offset), device="cuda")
+        out, h = torch.zeros((1, 256), device="cuda"), torch.zeros((1, 200, 256), device="cuda")
+        batch = Batch([EmbChunk(0, offset, n, True, "buffer")], [], ids, hidden_stride=200)
+        R.step(dm, dm, batch, dkv, dkv, S, Wc, None, out, ws, hidden=h)
+        torch.cuda.synchronize()
+        assert ws.device_error() == 0
+        hidden.append(h[0, offset:offset + n])
+    clean, got = hidden
+    assert torch.isfinite(clean).all()
+    assert float((got[:bad] - clean[:bad]).abs().max()) <= 1e-5 * float(clean.abs().max())
+    assert torch.isnan(got[bad:]).all()
