@@ -573,11 +573,14 @@ __global__ __launch_bounds__(256) void pool_rows_kernel(PoolArgs a) {
 }
 
 // ---- d <= 8192: the final norm and the pooler in one launch, plus two for chunks of several slices.
-// Blocks of two 256-thread groups: [0, ceil(n_lm / 2)) norm two LM rows each; then max_slices blocks
-// per chunk.  A mean, weighted-mean or buffered chunk is cut into slices of kPoolRows rows: the block
+// Blocks of two 256-thread groups: [0, ceil(n_lm / 2)) norm two LM rows each; then the chunks' blocks.
+// A mean, weighted-mean or buffered chunk is cut into slices of kPoolRows rows: the block
 // norms its rows (a group one row at a time, the next row and its pending slabs in flight) and sums
 // them in registers, so the rows are read once and never written back.  A chunk of one slice is
-// finished here, longer ones leave partial sums that pool_sum_slices adds.
+// finished here, longer ones leave partial sums that pool_sum_slices adds.  Even chunks get as many blocks
+// each as the longest has slices.  Where that is more than Te / kPoolRows + n_chunks blocks, chunk i's start
+// at its first row / kPoolRows + i, at least a block per slice, however uneven they are (2048-wide, 1024 rows
+// beside 1024 chunks of one row 560 us with blocks for the longest, 34 so; 128 chunks of 16 rows 17 and 23).
 // Single-row heads take their row in slice 0's block.  Norm, row pooler, accumulation and finish as
 // launches of their own took 62 us on three 512-row chunks, 51 us on 1024 rows of short queries; these
 // take 25 and 31 us.
@@ -623,9 +626,8 @@ __device__ __forceinline__ float sum_squares(const float4 (&v)[RV], int t, int n
 
 // out_emb of a final chunk from this thread's columns v0 + i * step of S: v / max(||v||, 1e-12)
 template <int NV>
-__device__ void finish_chunk(const PoolArgs &a, int ci, const float4 (&S)[NV], bool mine, int v0, int step, float W, float *red) {
-    const int32_t *ch = a.chunks + kChunkInts * ci;
-    const int flags = ch[3], nv = a.d / 4;
+__device__ void finish_chunk(const PoolArgs &a, int ci, int flags, const float4 (&S)[NV], bool mine, int v0, int step, float W, float *red) {
+    const int nv = a.d / 4;
     if (!(flags & ORTHRUS_CHUNK_LAST)) return;
     const float div = ((flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK) == ORTHRUS_POOL_MEAN ? W : 1.f;
     float4 v[NV];
@@ -650,10 +652,32 @@ __device__ __forceinline__ float4 add_gained(float4 S, float4 tot, float4 g) {
     return float4{S.x + tot.x * g.x, S.y + tot.y * g.y, S.z + tot.z * g.z, S.w + tot.w * g.w};
 }
 
-// the partial sums of chunk `ch`'s slices: disjoint per chunk, because a chunk of several slices has at
+// the partial sums of the slices of the chunk whose first row is t0: disjoint per chunk, because a chunk of several slices has at
 // most len / 4 of them, and at most Te / 4 rows of d floats in all
-__device__ __forceinline__ float *slice_row(const PoolArgs &a, const int32_t *ch, int sl) {
-    return a.part + (size_t)(ch[4] / 4 + sl) * a.d;
+__device__ __forceinline__ float *slice_row(const PoolArgs &a, int t0, int sl) {
+    return a.part + (size_t)(t0 / 4 + sl) * a.d;
+}
+
+struct ChunkSlice { int ci, sl, seq, off, len, flags, t0; };
+
+// The chunk whose blocks hold block b (the last one that starts at or before it), 64 candidates a step.  The
+// last step's lanes hold the whole descriptors, so up to 64 chunks cost one load as a known index does.
+__device__ __forceinline__ ChunkSlice chunk_of_block(const PoolArgs &a, int b) {
+    const int lane = threadIdx.x & 63;
+    for (int lo = 0, hi = a.n_chunks;;) {
+        const int step = (hi - lo + 63) / 64, i = lo + lane * step, j = min(i, a.n_chunks - 1);
+        int ch[kChunkInts];
+#pragma unroll
+        for (int k = 0; k < kChunkInts; ++k) ch[k] = a.chunks[kChunkInts * j + k];
+        const int first_block = ch[4] / kPoolRows + j;
+        const int at = __popcll(__ballot(i < hi && first_block <= b)) - 1;
+        if (step == 1) {
+            auto of = [&](int v) { return __builtin_amdgcn_readlane(v, at); };
+            return {lo + at, b - of(first_block), of(ch[0]), of(ch[1]), of(ch[2]), of(ch[3]), of(ch[4])};
+        }
+        lo += at * step;
+        hi = min(hi, lo + step);
+    }
 }
 
 template <typename T, int RV>
@@ -688,9 +712,15 @@ __global__ __launch_bounds__(512) void final_pool_kernel(PoolArgs a) {
         }
         return;
     }
-    const int ci = (blockIdx.x - lm_blocks) / a.max_slices, sl = (blockIdx.x - lm_blocks) % a.max_slices;
-    const int32_t *ch = a.chunks + kChunkInts * ci;
-    const int seq = ch[0], off = ch[1], len = ch[2], flags = ch[3], t0 = ch[4];
+    ChunkSlice cs;
+    if (a.max_slices == 0) {
+        cs = chunk_of_block(a, blockIdx.x - lm_blocks);
+    } else {
+        const int i = (blockIdx.x - lm_blocks) / a.max_slices;
+        const int32_t *ch = a.chunks + kChunkInts * i;
+        cs = {i, (int)(blockIdx.x - lm_blocks) % a.max_slices, ch[0], ch[1], ch[2], ch[3], ch[4]};
+    }
+    const int ci = cs.ci, sl = cs.sl, seq = cs.seq, off = cs.off, len = cs.len, flags = cs.flags, t0 = cs.t0;
     const int pool = (flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
     const bool sums = pool == ORTHRUS_POOL_MEAN || pool == ORTHRUS_POOL_WMEAN;
     if (!sums && pool != ORTHRUS_POOL_BUFFER) {
@@ -760,11 +790,11 @@ __global__ __launch_bounds__(512) void final_pool_kernel(PoolArgs a) {
             acc[i] = add_gained(off == 0 ? float4{0.f, 0.f, 0.f, 0.f} : load4(S), acc[i], load4(a.gain + 4 * c));
             store4(S, acc[i]);
         }
-        finish_chunk<RV>(a, ci, acc, grp == 0, t, 256, W, red);
+        finish_chunk<RV>(a, ci, flags, acc, grp == 0, t, 256, W, red);
         return;
     }
     if (grp == 0) {
-        float *dst = slice_row(a, ch, sl);
+        float *dst = slice_row(a, t0, sl);
 #pragma unroll
         for (int i = 0; i < RV; ++i)
             if (t + i * 256 < nv) store4(dst + 4 * (t + i * 256), acc[i]);
@@ -773,18 +803,22 @@ __global__ __launch_bounds__(512) void final_pool_kernel(PoolArgs a) {
 
 // S of the mean and weighted-mean chunks of several slices.  Grid (chunks, 64-float4 columns), sixteen
 // waves: wave w adds slices w, w + 16, ..., the waves' sums meet in LDS in wave order.  A thread that
-// walked all slices of its column waited on them 16 at a time (64 slices 22 us, this 4.7).
-constexpr int kSliceWaves = 16;
-__global__ __launch_bounds__(64 * kSliceWaves) void pool_sum_slices(PoolArgs a) {
-    __shared__ float4 part[kSliceWaves][64];
+// walked all slices of its column waited on them 16 at a time (64 slices 22 us, this 4.7).  With many
+// chunks a block takes every gridDim.x-th, having looked over 64 of them at once for those that it has
+// to do with (two rounds of blocks over the chip: kSumBlocks).
+constexpr int kSliceWaves = 16, kSumBlocks = 1024;
+__device__ __forceinline__ bool has_slices(const int32_t *ch) {
+    const int pool = (ch[3] >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
+    return (pool == ORTHRUS_POOL_MEAN || pool == ORTHRUS_POOL_WMEAN) && ch[2] > kPoolRows;
+}
+
+__device__ void sum_slices(const PoolArgs &a, int ci, float4 (&part)[kSliceWaves][64]) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ci = blockIdx.x, c = blockIdx.y * 64 + lane, nv = a.d / 4;
+    const int c = blockIdx.y * 64 + lane, nv = a.d / 4;
     const int32_t *ch = a.chunks + kChunkInts * ci;
-    const int seq = ch[0], off = ch[1], len = ch[2], flags = ch[3];
-    const int pool = (flags >> ORTHRUS_POOL_SHIFT) & ORTHRUS_POOL_MASK;
-    if ((pool != ORTHRUS_POOL_MEAN && pool != ORTHRUS_POOL_WMEAN) || len <= kPoolRows) return;
+    const int seq = ch[0], off = ch[1], len = ch[2];
     const int slices = (len + kPoolRows - 1) / kPoolRows;
-    const float *src = slice_row(a, ch, 0) + 4 * min(c, nv - 1);
+    const float *src = slice_row(a, ch[4], 0) + 4 * min(c, nv - 1);
     float *S = a.acc_sum + (size_t)seq * a.d + 4 * min(c, nv - 1);
     const float w_old = a.acc_w[seq];
     float4 g{}, old{0.f, 0.f, 0.f, 0.f};
@@ -813,6 +847,18 @@ __global__ __launch_bounds__(64 * kSliceWaves) void pool_sum_slices(PoolArgs a) 
     store4(S, add_gained(old, tot, g));
 }
 
+__global__ __launch_bounds__(64 * kSliceWaves) void pool_sum_slices(PoolArgs a) {
+    __shared__ float4 part[kSliceWaves][64];
+    for (int base = blockIdx.x; base < a.n_chunks; base += 64 * gridDim.x) {
+        const int i = base + (threadIdx.x & 63) * gridDim.x;
+        // the same in every wave
+        for (uint64_t todo = __ballot(i < a.n_chunks && has_slices(a.chunks + kChunkInts * min(i, a.n_chunks - 1))); todo; todo &= todo - 1) {
+            sum_slices(a, base + (__ffsll((unsigned long long)todo) - 1) * gridDim.x, part);
+            __syncthreads();
+        }
+    }
+}
+
 // then their token count and embedding, one block a chunk; buffered chunks: the token count
 constexpr int kFinishThreads = 1024;
 __global__ __launch_bounds__(kFinishThreads) void pool_finish_slices(PoolArgs a) {
@@ -839,7 +885,7 @@ __global__ __launch_bounds__(kFinishThreads) void pool_finish_slices(PoolArgs a)
     }
     const float W = (off == 0 ? 0.f : w_old) + (float)len;
     if (threadIdx.x == 0) a.acc_w[seq] = W;
-    if (sums) finish_chunk<NV>(a, ci, S, true, threadIdx.x, kFinishThreads, W, red);
+    if (sums) finish_chunk<NV>(a, ci, flags, S, true, threadIdx.x, kFinishThreads, W, red);
 }
 
 // ------------------------------------------------------------------------- greedy sampler
@@ -944,15 +990,21 @@ hipError_t launch_final_pool(int dtype, const PoolArgs &a, bool slices, hipStrea
     if (!final_pool_takes(a.d) || a.npend < 0 || a.npend > kMaxPend || a.max_len < 0) return hipErrorInvalidValue;
     PoolArgs q = a;
     q.max_slices = std::max(1, (a.max_len + kPoolRows - 1) / kPoolRows);
-    const long blocks = (a.n_lm + 1) / 2 + (long)a.n_chunks * q.max_slices;
+    long chunk_blocks = (long)a.n_chunks * q.max_slices;
+    if (chunk_blocks > a.Te / kPoolRows + a.n_chunks) {
+        chunk_blocks = a.Te / kPoolRows + a.n_chunks;
+        q.max_slices = 0;
+    }
+    const int blocks = (a.n_lm + 1) / 2 + (int)chunk_blocks;
     if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const bool rv4 = a.d <= 4096;
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(512), 0, s, q); };
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(blocks), dim3(512), 0, s, q); };
     if (dtype == 1) rv4 ? go(final_pool_kernel<bf16, 4>) : go(final_pool_kernel<bf16, 8>);
     else rv4 ? go(final_pool_kernel<float, 4>) : go(final_pool_kernel<float, 8>);
-    if (a.max_len > kPoolRows)
-        hipLaunchKernelGGL(pool_sum_slices, dim3(a.n_chunks, (a.d / 4 + 63) / 64), dim3(64 * kSliceWaves), 0, s, q);
+    if (a.max_len > kPoolRows) {
+        const int cols = (a.d / 4 + 63) / 64;
+        hipLaunchKernelGGL(pool_sum_slices, dim3(std::min(a.n_chunks, kSumBlocks / cols), cols), dim3(64 * kSliceWaves), 0, s, q);
+    }
     if (slices) hipLaunchKernelGGL(pool_finish_slices, dim3(a.n_chunks), dim3(kFinishThreads), 0, s, q);
     return hipGetLastError();
 }
