@@ -10,7 +10,8 @@
 // Tiles are mapped to blocks so that consecutive tiles of one weight column block land on
 // the same XCD (blocks are dealt round-robin to the 8 XCDs), which keeps re-reads of a
 // weight tile inside one L2.
-// fp32 path: v_mfma_f32_32x32x2_f32, one 32x32 tile per workgroup (exact checks, small models).
+// fp32 path: v_mfma_f32_32x32x2_f32, one 32x32 tile per workgroup, or two by two where many outputs fill
+// the chip with them (exact checks, small models).
 #include <algorithm>
 #include <type_traits>
 
@@ -329,46 +330,58 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_bf16_kernel(GemmArgs a) 
 // feeds them to four MFMAs, both operands in the same order.  The fp32 models are the small ones
 // (K <= 1024, a few hundred rows), where a call lasts as long as one workgroup's chain: short
 // K runs and many workgroups count (260 x 256 outputs, K 256 and 1024: 69 us on average on 64x64
-// LDS tiles of scalar FMAs with 20 workgroups, 8.9 us with 72 of these; 512 rows through a 7B-shape
-// layer 8.2 -> 5.0 ms).
+// LDS tiles of scalar FMAs with 20 workgroups, 8.9 us with 72 of these).
+// TWO: two row tiles by two weight tiles (or by gate and up) per wave, where the outputs fill the chip with
+// them (run_f32).  What bounds one tile there is the rate of its loads, which touch 32 rows for 1 KB: two
+// need half the loads per MFMA (7B shape, 512 rows: gate/up 2333 -> 1683 us, QKV 520 -> 371; 2048 rows: 9160 ->
+// 6416, 2021 -> 1400; LM head of 256 rows 1688 -> 976).  Each output is summed in the same order either way.
 constexpr int kF32Waves = 8, kF32Run = 4;   // waves; 16-byte loads per operand and register set
-template <int EPI>
+template <int EPI, bool TWO>
 __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(GemmArgs a) {
-    constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
+    constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;       // weight matrices
+    constexpr int RM = TWO ? 2 : 1, RN = TWO && NB == 1 ? 2 : 1, RB = NB * RN;
     __shared__ float red[kF32Waves][NB][32 * 33];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32, half = lane >> 5;
+    // one tile: weight tiles fastest; two: row tiles fastest, so that large weights leave HBM once
+    const int m0 = (TWO ? blockIdx.x : blockIdx.y) * (32 * RM), n0 = (TWO ? blockIdx.y : blockIdx.x) * (32 * RN), half = lane >> 5;
     const int chunks = a.K / 8;                       // runs of 8 k: 4 for each half of the wave
     const int c0 = wave * chunks / kF32Waves, c1 = (wave + 1) * chunks / kF32Waves;
-    const float *pa = (const float *)a.A + (size_t)min(m0 + (lane & 31), a.M - 1) * a.lda + 4 * half;
-    const float *pb[NB];
-    pb[0] = (const float *)a.B0 + (size_t)min(n0 + (lane & 31), a.N - 1) * a.K + 4 * half;
-    if (NB == 2) pb[NB - 1] = (const float *)a.B1 + (size_t)min(n0 + (lane & 31), a.N - 1) * a.K + 4 * half;
-    f32x16 acc[NB];
+    const float *pa[RM], *pb[RB];
 #pragma unroll
-    for (int x = 0; x < NB; ++x)
+    for (int i = 0; i < RM; ++i) pa[i] = (const float *)a.A + (size_t)min(m0 + 32 * i + (lane & 31), a.M - 1) * a.lda + 4 * half;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[x][e] = 0.f;
-    f32x4 va[2][kF32Run], vb[2][NB][kF32Run];
+    for (int j = 0; j < RB; ++j)
+        pb[j] = (const float *)(NB == 2 && j ? a.B1 : a.B0) + (size_t)min(n0 + (NB == 2 ? 0 : 32 * j) + (lane & 31), a.N - 1) * a.K + 4 * half;
+    f32x16 acc[RM][RB];
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    f32x4 va[2][RM][kF32Run], vb[2][RB][kF32Run];
     // runs [c, c + kF32Run) of this wave into set s, as many as it has
     auto load = [&](int c, int s) {
 #pragma unroll
-        for (int i = 0; i < kF32Run; ++i) {
-            if (c + i >= c1) break;
-            va[s][i] = *(const f32x4 *)(pa + 8 * (c + i));
+        for (int k = 0; k < kF32Run; ++k) {
+            if (c + k >= c1) break;
 #pragma unroll
-            for (int x = 0; x < NB; ++x) vb[s][x][i] = *(const f32x4 *)(pb[x] + 8 * (c + i));
+            for (int i = 0; i < RM; ++i) va[s][i][k] = *(const f32x4 *)(pa[i] + 8 * (c + k));
+#pragma unroll
+            for (int j = 0; j < RB; ++j) vb[s][j][k] = *(const f32x4 *)(pb[j] + 8 * (c + k));
         }
     };
     auto mul = [&](int c, int s) {
 #pragma unroll
-        for (int i = 0; i < kF32Run; ++i) {
-            if (c + i >= c1) break;
+        for (int k = 0; k < kF32Run; ++k) {
+            if (c + k >= c1) break;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int x = 0; x < NB; ++x)
-                    acc[x] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[s][i][e], vb[s][x][i][e], acc[x], 0, 0, 0);
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[s][i][k][e], vb[s][j][k][e], acc[i][j], 0, 0, 0);
         }
     };
     load(c0, 0);
@@ -378,40 +391,60 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_kernel(GemmArgs a) {
         load(c + 2 * kF32Run, 0);
         mul(c + kF32Run, 1);
     }
-    // lane holds column lane % 32, rows 8 (e / 4) + 4 (lane / 32) + e % 4
 #pragma unroll
-    for (int x = 0; x < NB; ++x)
+    for (int i = 0; i < RM; ++i)
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-            red[wave][x][((e >> 2) * 8 + half * 4 + (e & 3)) * 33 + (lane & 31)] = acc[x][e];
-    __syncthreads();
-    for (int o = tid; o < 32 * 32; o += 64 * kF32Waves) {
-        const int r = o / 32, c = o % 32, row = m0 + r, col = n0 + c;
-        if (row >= a.M || col >= a.N) continue;
-        float v[NB];
+        for (int j = 0; j < RN; ++j) {
+            if (i + j > 0) __syncthreads();           // the tile before has been read
+            // lane holds column lane % 32, rows 8 (e / 4) + 4 (lane / 32) + e % 4
 #pragma unroll
-        for (int x = 0; x < NB; ++x) {
-            v[x] = red[0][x][r * 33 + c];
+            for (int x = 0; x < NB; ++x)
 #pragma unroll
-            for (int w = 1; w < kF32Waves; ++w) v[x] += red[w][x][r * 33 + c];
-        }
-        if (a.lora.n > 0 && row < a.lora.rows) {      // LoRA update U B^T
-            const LoraGemm &L = a.lora;
-            const int ldu = L.n * L.r;
-            const float *u = (const float *)L.u + (size_t)row * ldu;
+                for (int e = 0; e < 16; ++e)
+                    red[wave][x][((e >> 2) * 8 + half * 4 + (e & 3)) * 33 + (lane & 31)] = acc[i][NB == 2 ? x : j][e];
+            __syncthreads();
+            for (int o = tid; o < 32 * 32; o += 64 * kF32Waves) {
+                const int r = o / 32, c = o % 32, row = m0 + 32 * i + r, col = n0 + 32 * j + c;
+                if (row >= a.M || col >= a.N) continue;
+                float v[NB];
 #pragma unroll
-            for (int x = 0; x < NB; ++x) {
-                float d = 0.f;
-                for (int i = 0; i < ldu; ++i)
-                    d = fmaf(u[i], ((const float *)(x ? L.b1 : L.b0)[i / L.r])[(size_t)col * L.r + i % L.r], d);
-                v[x] += d;
+                for (int x = 0; x < NB; ++x) {
+                    v[x] = red[0][x][r * 33 + c];
+#pragma unroll
+                    for (int w = 1; w < kF32Waves; ++w) v[x] += red[w][x][r * 33 + c];
+                }
+                if (a.lora.n > 0 && row < a.lora.rows) {      // LoRA update U B^T
+                    const LoraGemm &L = a.lora;
+                    const int ldu = L.n * L.r;
+                    const float *u = (const float *)L.u + (size_t)row * ldu;
+#pragma unroll
+                    for (int x = 0; x < NB; ++x) {
+                        float d = 0.f;
+                        for (int k = 0; k < ldu; ++k)
+                            d = fmaf(u[k], ((const float *)(x ? L.b1 : L.b0)[k / L.r])[(size_t)col * L.r + k % L.r], d);
+                        v[x] += d;
+                    }
+                }
+                float *out = (float *)a.out + (size_t)row * a.ldo + col;
+                if (EPI == EPI_SWIGLU) *out = silu(v[0]) * v[NB - 1];
+                else if (EPI == EPI_ADD_F32) *out += v[0];
+                else *out = v[0];
             }
         }
-        float *out = (float *)a.out + (size_t)row * a.ldo + col;
-        if (EPI == EPI_SWIGLU) *out = silu(v[0]) * v[NB - 1];
-        else if (EPI == EPI_ADD_F32) *out += v[0];
-        else *out = v[0];
-    }
+}
+
+// Two tiles where their rounds of workgroups over the chip take less time: a round of them lasts as long as
+// 3.1 of one tile each, 1.6 for gate/up (K 4096: 134 us against 43, 137 against 84).  256 rows by 4096, one
+// round against four: 173 -> 136 us; 160 by 6144, two against four: 179 stays, 240 on two.
+template <int EPI>
+hipError_t run_f32(const GemmArgs &a, hipStream_t s) {
+    constexpr bool sw = EPI == EPI_SWIGLU;
+    constexpr int cols = sw ? 32 : 64;
+    const dim3 one((a.N + 31) / 32, (a.M + 31) / 32), two((a.M + 63) / 64, (a.N + cols - 1) / cols), block(64 * kF32Waves);
+    auto rounds = [](const dim3 &g) { return ((long)g.x * g.y + 255) / 256; };
+    if (rounds(two) * (sw ? 16 : 31) < rounds(one) * 10) hipLaunchKernelGGL((gemm_f32_kernel<EPI, true>), two, block, 0, s, a);
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, false>), one, block, 0, s, a);
+    return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, int BKS = 64, int STAGES = 2, int BSTAGES = STAGES,
@@ -607,13 +640,11 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
             default: return dispatch_bf16<EPI_SWIGLU>(a, s);
         }
     }
-    const dim3 grid((a.N + 31) / 32, (a.M + 31) / 32), block(64 * kF32Waves);
     switch (epi) {
-        case EPI_STORE_F32: hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE_F32>, grid, block, 0, s, a); break;
-        case EPI_ADD_F32: hipLaunchKernelGGL(gemm_f32_kernel<EPI_ADD_F32>, grid, block, 0, s, a); break;
-        default: hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, s, a); break;
+        case EPI_STORE_F32: return run_f32<EPI_STORE_F32>(a, s);
+        case EPI_ADD_F32: return run_f32<EPI_ADD_F32>(a, s);
+        default: return run_f32<EPI_SWIGLU>(a, s);
     }
-    return hipGetLastError();
 }
 
 }  // namespace orthrus
