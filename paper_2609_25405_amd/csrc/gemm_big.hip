@@ -326,25 +326,33 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_big_kernel(GemmArgs a, Bi
 #endif
 }
 
-// time of the last of n1 tiles of cost c1, then n2 of cost c2, handed in order to 256 CUs as
-// they become free
-double makespan(long n1, double c1, long n2, double c2) {
-    const long r = n1 / 256, k = n1 % 256;
-    const double ta = r * c1, tb = ta + c1;          // 256 - k CUs are free at ta, k at tb
-    double end = k ? tb : ta;
-    if (n2 == 0) return end;
-    // the least time by which the CUs finish n2 more tiles: a tile's end on one of the two groups
-    double best = -1.0;
-    for (long i = 0; best < 0.0; ++i) {
-        const double at[2] = {ta + i * c2, tb + i * c2};
-        for (const double t : at) {
-            if (k == 0 && t != at[0]) continue;
-            const long done = (long)((t - ta) / c2 + 1e-9) * (256 - k) + (t > tb ? (long)((t - tb) / c2 + 1e-9) * k : 0);
-            if (done >= n2 && (best < 0.0 || t < best)) best = t;
+// Tiles of two costs handed in order, the first kind before the second, to 256 CUs as they become free
+struct TwoCosts {
+    double c1, c2, ratio, inv2;
+    TwoCosts(double first, double second) : c1(first), c2(second), ratio(first / second), inv2(1 / second) {}
+    // whether the last of n1 and n2 tiles can end before `limit`: n2 tiles' worth of the CUs' time after their
+    // first kind
+    bool can_end_before(double limit, long n1, long n2) const {
+        const long k = n1 % 256;
+        const double after_a = (limit - n1 / 256 * c1) * inv2 + 1e-6, after_b = after_a - ratio;
+        return after_a > 0 && (long)after_a * (256 - k) + (after_b > 0 ? (long)after_b * k : 0) >= n2;
+    }
+    // the time of the last
+    double makespan(long n1, long n2) const {
+        const long k = n1 % 256;
+        const double ta = n1 / 256 * c1, tb = ta + c1;   // 256 - k CUs are free at ta, k at tb
+        const double end = k ? tb : ta;
+        if (n2 == 0) return end;
+        // the least time by which the CUs finish n2 more tiles: a tile's end on one of the two groups
+        const double average = (n1 * c1 + n2 * c2) * (1.0 / 256);     // load of a CU: no end is before it
+        for (long i = std::max(0L, (long)((average - tb) * inv2) - 1);; ++i) {
+            // by ta + i c2, by tb + i c2
+            const double by_a = i - ratio + 1e-9, by_b = i + ratio + 1e-9;
+            if (i * (256 - k) + (by_a > 0 ? (long)by_a * k : 0) >= n2) return std::max(end, ta + i * c2);
+            if (k && (long)by_b * (256 - k) + i * k >= n2) return std::max(end, tb + i * c2);
         }
     }
-    return std::max(end, best);
-}
+};
 
 // Microseconds of a K stage of a bm x bn tile, and of the rest of a tile (prologue, epilogue).
 // Measured over the 7B and the 2048-wide shapes at 160..2048 rows: 256x256 1.45, 256x192 and
@@ -376,7 +384,7 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits, bool li
     best.m_main = mt;
     best.n_main = nt;
     best.splits = splits;
-    best.us = light ? 1e30 : makespan((long)mt * nt * splits, c256, 0, 0.0);
+    best.us = light ? 1e30 : TwoCosts(c256, c256).makespan((long)mt * nt * splits, 0);
     auto offer = [&](const BigPlan &p) {
         if (p.us < best.us * 0.98) best = p;
     };
@@ -392,49 +400,65 @@ static BigPlan search_plan(int M, int N, int K, bool swiglu, int splits, bool li
         p.n_alt = nt;
         p.row_alt = M - rem;
         p.splits = splits;
-        p.us = makespan((long)p.m_main * nt * splits, c256, (long)nt * splits, tile_us(bm, 256));
+        p.us = TwoCosts(c256, tile_us(bm, 256)).makespan((long)p.m_main * nt * splits, (long)nt * splits);
         offer(p);
     }
     // columns past the first j column tiles on 192- or 128-wide tiles
     for (int shape = 2; shape <= 3 && !light; ++shape) {
         const int w = (shape == 2 ? 192 : 128) / f;
+        const double inv_w = 1.0 / w;
+        const TwoCosts costs(c256, tile_us(256, w * f));
         for (int j = 0; j < nt; ++j) {
+            const int n_alt = (int)((N - j * C + w - 0.5) * inv_w);      // the quotient rounded up
+            const long n1 = (long)mt * j * splits, n2 = (long)mt * n_alt * splits;
+            if (((n1 + 255) >> 8) * c256 >= best.us * 0.98) break;       // the first kind's end alone
+            if (!costs.can_end_before(best.us * 0.98, n1, n2)) continue;
             BigPlan p;
+            p.us = costs.makespan(n1, n2);
             p.shape = shape;
             p.m_main = mt;
             p.n_main = j;
             p.m_alt = mt;
-            p.n_alt = (N - j * C + w - 1) / w;
+            p.n_alt = n_alt;
             p.col_alt = j * C;
             p.splits = splits;
-            p.us = makespan((long)mt * j * splits, c256, (long)mt * p.n_alt * splits, tile_us(256, w * f));
             offer(p);
         }
     }
     for (const Shape &sh : kAlone) {
         if (light && !sh.light) continue;
-        BigPlan p;
-        p.shape = sh.id;
-        p.m_alt = (M + sh.bm - 1) / sh.bm;
-        p.n_alt = (N + sh.bn / f - 1) / (sh.bn / f);
-        p.splits = splits;
-        const long n = (long)p.m_alt * p.n_alt * splits, slots = 256L * sh.per_cu, left = n % slots;
+        const int cols = sh.bn / f, m_alt = (M + sh.bm - 1) / sh.bm, n_alt = (N + cols - 1) / cols;
+        const unsigned n = (unsigned)m_alt * n_alt * splits, slots = 256u << (sh.per_cu - 1);
+        const unsigned left = n & (slots - 1);
         const double full = stages * stage_us(sh.bm, sh.bn, sh.per_cu) + kTileUs;
-        p.us = n / slots * full + (left == 0 ? 0.0 : left <= 256 ? tile_us(sh.bm, sh.bn) : full);
-        offer(p);
+        BigPlan p;
+        p.us = (n >> (7 + sh.per_cu)) * full + (left == 0 ? 0.0 : left <= 256 ? tile_us(sh.bm, sh.bn) : full);
+        if (p.us >= best.us * 0.98) continue;
+        p.shape = sh.id;
+        p.m_alt = m_alt;
+        p.n_alt = n_alt;
+        p.splits = splits;
+        best = p;
     }
     return best;
 }
 
-// The search takes a few microseconds; a layer asks for the same four covers as the one before it, so
-// each thread keeps the last ones it computed (a pure function of the sizes).
+// The search takes up to a microsecond or two; a layer asks for the same covers (about eleven) as the one
+// before it, so each thread keeps the last ones it computed (a pure function of the sizes), four to a set.
 BigPlan plan_big(int M, int N, int K, bool swiglu, int splits, bool light) {
-    struct Entry { int M = -1, N = 0, K = 0, sw = 0, splits = 0, light = 0; BigPlan plan; };
-    static thread_local Entry memo[64];
-    const unsigned h = (unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)(splits * 4 + swiglu * 2 + light) * 668265263u;
-    Entry &e = memo[h >> 26];
-    if (e.M != M || e.N != N || e.K != K || e.sw != (int)swiglu || e.splits != splits || e.light != (int)light)
-        e = Entry{M, N, K, (int)swiglu, splits, (int)light, search_plan(M, N, K, swiglu, splits, light)};
+    struct Entry { int M = 0, N = 0, K = 0, rest = -1; BigPlan plan; };
+    constexpr int kSets = 32, kWays = 4;
+    static thread_local Entry memo[kSets][kWays];
+    static thread_local unsigned char oldest[kSets];
+    const int rest = splits * 4 + swiglu * 2 + light;
+    uint64_t h = (uint64_t)(unsigned)M << 32 | (unsigned)N;
+    for (const uint64_t part : {(uint64_t)(unsigned)K, (uint64_t)(unsigned)rest}) h = ((h ^ h >> 29) + part) * 0x9e3779b97f4a7c15u;
+    const int set = (int)(h >> 59);
+    static_assert(kSets == 32, "five bits of the hash");
+    for (const Entry &e : memo[set])
+        if (e.M == M && e.N == N && e.K == K && e.rest == rest) return e.plan;
+    Entry &e = memo[set][oldest[set]++ % kWays];
+    e = Entry{M, N, K, rest, search_plan(M, N, K, swiglu, splits, light)};
     return e.plan;
 }
 
