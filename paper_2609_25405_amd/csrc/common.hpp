@@ -86,8 +86,9 @@ struct GemmArgs {
     int b_blocked;
     // The launch's company.  0: none that matters; 1, 2: another stream's launches run beside it, so
     // it leaves registers and LDS to that stream's small kernels: with 1 (every group of at most 896
-    // rows) on the large kernel's light tile shapes, with 2 on the 256-row tiles of gemm.hip,
-    // whose workgroup time per flop is the least of those that leave room
+    // rows) on the large kernel's light tile shapes (at most 112 KB of LDS) where it goes there at all (up
+    // to 256 rows it may stay on gemm.hip's rings of 128 or 144 KB, see dispatch_bf16), with 2 on the 256-row
+    // tiles of gemm.hip, whose workgroup time per flop is the least of those that leave room
     int wide;
 };
 hipError_t launch_gemm(int dtype, int epilogue, const GemmArgs &a, hipStream_t s);

@@ -496,7 +496,8 @@ bool ring_split(int M, int N, int K, int splits) {
 //  - beside another stream's launches the large kernel's 256-row tiles leave no registers and no LDS
 //    for that stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against 5.99 ms).
 //    Groups of at most 896 rows (GemmArgs::wide 1) take its light shapes (two models, 4 layers, 512 +
-//    256 rows 2.58 -> 2.47 ms, 256 + 64 rows 1.43 -> 1.39 against this file's tiles); beside larger
+//    256 rows 2.58 -> 2.47 ms, 256 + 64 rows 1.43 -> 1.39 against this file's tiles; groups of at most 256
+//    rows as above, so on 128 or 144 KB of LDS where this file's tiles are the shorter alone); beside larger
 //    groups (wide 2) this file's tiles stay: split-K projections of 129..256 rows and of more than
 //    896 on 256x256 (fewest workgroup-microseconds per flop; the other stream's launches fill the
 //    rest; the light shapes take 6.75 instead of 5.99 ms), gate/up above 256 rows on the 192x256,
