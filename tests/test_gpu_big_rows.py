@@ -2,12 +2,15 @@
 row counts on and beside the edges of its tiles: one row past the smallest batch it takes, row
 counts that its covers give to 64-, 128- and 192-row tiles, a last row tile of one row, of exactly
 64, 128 and of 129 rows, whole tiles, and enough rows for several rounds; with LoRA adapters on part of the rows (ranks 16 and 48,
-so that a 32-column step of the update ends inside and past an adapter's block)."""
+so that a 32-column step of the update ends inside and past an adapter's block).  Each case names the K splits
+and covers that its four projections take, every cover of the kernel among them: a change of the rules
+that loses one shows here."""
 import numpy as np
 import pytest
 import torch
 
 from tests.parity import Pair
+from tests.test_covers import covers
 from workload import Batch, DecodeRow, EmbChunk, ModelConfig, PagedKV, draw_tokens, make_lora, make_weights
 
 pytestmark = pytest.mark.gpu
@@ -20,15 +23,30 @@ def _need_gpu(request):
     print(f"\n[case] {request.node.name}", flush=True)
 
 
-# (rows, rank, d_ff): the wide MLPs have enough column tiles for the two-shape covers (last rows on 128-
-# and 64-row tiles, last columns on 192-wide ones)
-@pytest.mark.parametrize("rows,rank,ff", [
-    (129, 0, 2816), (193, 16, 2816), (257, 0, 2816), (449, 48, 2816), (640, 0, 2816), (832, 0, 2816),
-    (897, 0, 2816), (1025, 0, 2816), (1088, 0, 2816), (1152, 16, 2816), (1281, 48, 2816), (1536, 0, 2816),
-    (2049, 0, 2816), (300, 0, 28672), (700, 16, 28672), (1025, 0, 28672), (1100, 48, 28672)])
-def test_rows(rows, rank, ff):
-    cfg = ModelConfig(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=ff, vocab=512,
-                      dtype="bf16")
+# rows, rank, d_model, d_ff, then (K splits, cover) of QKV, o, gate/up and down: the wide MLPs have enough
+# column tiles for the two-shape covers (last rows on 128- and 64-row tiles, last columns on 192- and 128-wide
+# ones), the 4096-wide models (16 query, 4 key/value heads; 7B-class at qkv 6144) for those with split K
+@pytest.mark.parametrize("rows,rank,d,ff,taken", [
+    (129, 0, 512, 2816, "1:10 2:10 1:10 4:10"), (193, 16, 512, 2816, "1:10 2:10 1:10 4:10"),
+    (257, 0, 512, 2816, "1:10 2:10 1:10 4:10"), (449, 48, 512, 2816, "1:10 2:10 1:8 4:10"),
+    (640, 0, 512, 2816, "1:10 2:10 1:8 4:10"), (832, 0, 512, 2816, "1:10 2:10 1:6 4:10"),
+    (897, 0, 512, 2816, "1:10 2:10 1:6 4:10"), (1025, 0, 512, 2816, "1:10 2:10 1:3 4:8"),
+    (1088, 0, 512, 2816, "1:10 2:10 1:3 4:8"), (1152, 16, 512, 2816, "1:10 2:10 1:3 4:8"),
+    (1281, 48, 512, 2816, "1:10 2:10 1:7 4:8"), (1536, 0, 512, 2816, "1:8 2:10 1:5 4:8"),
+    (2049, 0, 512, 2816, "1:8 2:8 1:4 4:6"), (300, 0, 512, 28672, "1:10 2:10 1:11 4:10"),
+    (700, 16, 512, 28672, "1:10 2:10 1:2 4:10"), (1025, 0, 512, 28672, "1:10 2:10 1:11 4:8"),
+    (1100, 48, 512, 28672, "1:10 2:10 1:1 4:8"), (1024, 0, 512, 8192, "1:10 2:10 1:0 4:10"),
+    (288, 16, 4096, 512, "2:9 4:6 1:10 1:10"), (512, 48, 4096, 512, "2:3 4:3 1:10 1:10")])
+def test_rows(rows, rank, d, ff, taken):
+    nq, nkv = (8, 2) if d == 512 else (32, 8)
+    plan_big, add_splits, qkv_splits = covers()
+    got = []
+    for N, K, sw, splits in (((nq + 2 * nkv) * 128, d, False, qkv_splits(rows, (nq + 2 * nkv) * 128, d, False)),
+                             (d, nq * 128, False, add_splits(rows, d, nq * 128, 4, False)), (ff, d, True, 1),
+                             (d, ff, False, add_splits(rows, d, ff, 4, False))):
+        got.append(f"{splits}:{plan_big(rows, N, K, sw, splits, False).shape}")
+    assert " ".join(got) == taken
+    cfg = ModelConfig(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=128, d_ff=ff, vocab=512, dtype="bf16")
     W = make_weights(cfg, 11)
     if rank:
         W["adapters"] = [make_lora(cfg, 5, rank, tag=i) for i in range(2)]
