@@ -3,12 +3,13 @@ oracle: chunks that end on, before and after a 32-key block and a 32-row wave, a
 keys pass the staged window of 512 pages, decode rows on both sides of the 64-key pass and of
 the 256-key split, projections whose eight K slices hold unequal runs (K = 320) or fewer than one
 round (K = 64), and caches whose base is only element-aligned; projections of many outputs on two
-tiles a wave, and their cost; a token whose keys and values are not
+tiles a wave, and their cost; a page that is not in the pool; a token whose keys and values are not
 numbers, which no earlier row of its chunk may see."""
 import pytest
 import torch
 
 from tests.parity import Pair
+from paper_2609_25405_amd import _abi as A
 from paper_2609_25405_amd import runtime as R
 from workload import Batch, DecodeRow, EmbChunk, ModelConfig, PagedKV, draw_tokens, make_lora, make_weights
 
@@ -87,6 +88,36 @@ def test_rows_before_a_token_that_is_not_a_number(nq, nkv, hd, offset, n, bad):
     assert torch.isfinite(clean).all()
     assert float((got[:bad] - clean[:bad]).abs().max()) <= 1e-5 * float(clean.abs().max())
     assert torch.isnan(got[bad:]).all()
+
+
+def test_bad_page():
+    """A chunk with a page past the pool: flagged; its rows before the page and the other chunk are as in a run
+    with the page in place, its other rows leave the page out."""
+    cfg = config(256, 4, 2, 128, 128)
+    W = make_weights(cfg, 24)
+    results = []
+    for bad in (False, True):
+        kv = PagedKV(cfg, 20, 2, 8, 4)
+        kv.reserve(0, 100)
+        kv.reserve(1, 50)
+        dm, dkv = R.DeviceModel(cfg, W), R.DeviceKV.from_paged(kv)
+        bt = kv.block_table.copy()
+        if bad:
+            bt[0, 3] = kv.n_pages
+        dkv.set_block_table(bt)
+        ws = R.Workspace(dm, dm, 150, 2, 0, 1)
+        S, Wc = torch.zeros((2, 256), device="cuda"), torch.zeros(2, device="cuda")
+        out, h = torch.zeros((2, 256), device="cuda"), torch.zeros((2, 100, 256), device="cuda")
+        batch = Batch([EmbChunk(0, 0, 100, True, "buffer"), EmbChunk(1, 0, 50, True, "buffer")], [], draw_tokens(9, 0, 150, 96),
+                      hidden_stride=100)
+        R.step(dm, dm, batch, dkv, dkv, S, Wc, None, out, ws, hidden=h)
+        torch.cuda.synchronize()
+        assert ws.device_error() == (A.ORTHRUS_DEVERR_PAGE if bad else 0)
+        results.append(h)
+    good, got = results
+    assert torch.isfinite(got).all()
+    assert torch.equal(got[1], good[1]) and torch.equal(got[0, :48], good[0, :48])
+    assert not torch.equal(got[0, 48:], good[0, 48:])
 
 
 # Outputs that fill the chip with two tiles a wave (64 x 64 outputs, 64 x 32 for gate/up), rows and columns
