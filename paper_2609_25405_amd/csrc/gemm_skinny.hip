@@ -4,9 +4,9 @@
 // pairs: gate and up, the two halves of a rotation), its eight waves split K, and each wave loads its
 // operands straight into registers in the layout of v_mfma_f32_16x16x32_bf16, up to sixteen K
 // steps ahead.  The eight partial tiles meet in LDS and are summed in wave order, and the
-// epilogues finish the row: residual add, SwiGLU, rotation with the cache append.  Where the rows
-// are small enough the launch also norms them itself, under the first weights' latency
-// (skinny_norms).  4 rows of a 512-wide 8-layer model: 8 launches a layer -> 5 and a step 364 -> 227
+// epilogues finish the row: residual add, SwiGLU, rotation with the cache append.  The launch also norms
+// complete rows of x itself, under the first weights' latency: each workgroup reads all rows twice for it,
+// from L2, at most 8.4 MB at the sizes skinny_takes allows, a microsecond beside a norm launch of 3 to 5 us.  4 rows of a 512-wide 8-layer model: 8 launches a layer -> 5 and a step 364 -> 227
 // us (projections 5.5 to 10.4 us on the tiled kernels, 3.7 to 5.7 here).
 //
 // Larger weights stay on the tiled kernels, whose copies to LDS move whole 128-byte lines: one row of
@@ -200,10 +200,6 @@ bool skinny_takes(int M, int weight_rows, int K) {
     // longer do (178.3 against 182.8 us); at 2 MB all do
     return M <= kSkinnyRows && K % 32 == 0 && (size_t)weight_rows * K * 2 <= (size_t)(M <= 4 ? 16 : 4) << 20;
 }
-
-// Each workgroup reads all rows twice (8 K M bytes, from L2): worth it while that is little beside a
-// norm launch of about 3 to 5 us (16 MB at some 8 TB/s)
-bool skinny_norms(int M, int weight_rows, int K) { return (double)weight_rows / 32 * M * K * 8 <= 16e6; }
 
 hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;

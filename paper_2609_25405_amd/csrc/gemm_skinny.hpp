@@ -25,7 +25,5 @@ struct SkinnyArgs {
 hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s);
 // whether the launch belongs here rather than on the tiled kernels (bf16; weight rows of K each)
 bool skinny_takes(int M, int weight_rows, int K);
-// whether a launch may norm its rows itself instead of a norm launch before it
-bool skinny_norms(int M, int weight_rows, int K);
 
 }  // namespace orthrus

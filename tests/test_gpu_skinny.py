@@ -1,12 +1,16 @@
 """Steps of at most 16 rows per model through small weights (the projections of gemm_skinny.hip) against
 the float64 oracle: 1, 4, 5, 16 rows and, past the rule, 17; head_dim 64 and 128 (two and four
-16-dim parts of a rotation half); K that is not a multiple of the waves' 32-deep steps (768) and deep
-enough for several rounds of loads (2816); rows the launch norms itself and rows normed before it
-(16 rows of a 2048-wide model); prompt rows, embedding rows and decode rows together; a vocabulary
-that ends inside a set of 16; two models."""
+16-dim parts of a rotation half); K that does not divide over the eight waves (768); K of several rounds of
+loads, ending inside one (down of 4864: 19 steps a wave, two rounds of 16; rows normed in the launch, 2304:
+9 steps, two rounds of 8); rows normed in the launch, with the gather (layer 0), and by a launch of
+their own before gate/up (an o projection whose weights are too large leaves partial sums); prompt rows,
+embedding rows and decode rows together; a vocabulary that ends inside a set of 16; two models; a
+row whose page is not in the pool."""
 import pytest
 import torch
 
+from paper_2609_25405_amd import _abi as A
+from paper_2609_25405_amd import runtime as R
 from tests.parity import Pair
 from workload import Batch, DecodeRow, EmbChunk, GenChunk, ModelConfig, PagedKV, draw_tokens, make_weights
 
@@ -27,11 +31,16 @@ def config(d, nq, nkv, hd, ff, vocab=100):
 NARROW = config(512, 8, 2, 128, 2816)
 ODD = config(768, 12, 12, 64, 768)
 WIDE = config(2048, 4, 2, 128, 512)
+DEEP = config(512, 8, 2, 128, 4864)
+DEEP_NORMED = config(2304, 2, 1, 128, 256)
+LARGE_O = config(512, 64, 16, 128, 256)     # o: 8 MB of weights, too much for more than 4 rows
 
 
 @pytest.mark.parametrize("cfg,emb,prompt,rows,two", [
     (NARROW, 0, 0, 1, False), (NARROW, 0, 0, 4, False), (NARROW, 7, 4, 5, False), (NARROW, 0, 0, 17, False),
-    (ODD, 1, 2, 2, False), (ODD, 6, 0, 10, True), (WIDE, 0, 0, 4, False), (WIDE, 3, 3, 10, False)])
+    (ODD, 1, 2, 2, False), (ODD, 6, 0, 10, True), (WIDE, 0, 0, 4, False), (WIDE, 3, 3, 10, False),
+    (DEEP, 0, 0, 4, False), (DEEP, 1, 0, 2, False), (DEEP_NORMED, 0, 0, 3, False), (DEEP_NORMED, 3, 2, 2, False),
+    (LARGE_O, 0, 0, 7, False)])
 def test_few_rows(cfg, emb, prompt, rows, two):
     W = make_weights(cfg, 31, model_tag=1)
     n0 = (1 if emb else 0)
@@ -55,3 +64,38 @@ def test_few_rows(cfg, emb, prompt, rows, two):
     pair = Pair(cfg, W, kv, cfg, make_weights(cfg, 32, model_tag=2), gkv) if two else Pair(cfg, W, kv)
     pair.workspace(emb + prompt + rows, 2, rows, 151)
     pair.step(batch)
+
+
+def test_bad_page():
+    """The launch that appends flags the row whose page is past the pool and writes nothing for it; the other
+    rows and every other slot are as in a run with its page in place."""
+    cfg = NARROW
+    W = make_weights(cfg, 31)
+    ctx = [40, 33, 7]
+    results = []
+    for bad in (False, True):
+        kv = PagedKV(cfg, 20, 3, 4, 8)
+        for j, c in enumerate(ctx):
+            kv.fill_random(j, c, 4)
+            kv.reserve(j, c + 1)
+        dm, dkv = R.DeviceModel(cfg, W), R.DeviceKV.from_paged(kv)
+        bt = kv.block_table.copy()
+        own = int(bt[1, 2])
+        if bad:
+            bt[1, 2] = kv.n_pages
+        dkv.set_block_table(bt)
+        before = [dkv.k.clone(), dkv.v.clone()]
+        ws = R.Workspace(dm, dm, 3, 0, 3, 64)
+        logits = torch.zeros((3, cfg.vocab), device="cuda")
+        R.step(dm, dm, Batch([], [DecodeRow(j, c) for j, c in enumerate(ctx)], draw_tokens(6, 0, 3, cfg.vocab)), dkv, dkv, None, None,
+               logits, None, ws)
+        torch.cuda.synchronize()
+        assert ws.device_error() == (A.ORTHRUS_DEVERR_PAGE if bad else 0)
+        results.append((logits, dkv.k, dkv.v, before))
+    (good_l, good_k, good_v, _), (bad_l, bad_k, bad_v, before) = results
+    assert torch.isfinite(bad_l).all()
+    assert torch.equal(good_l[[0, 2]], bad_l[[0, 2]])
+    bits = lambda t: t.view(torch.int16)
+    others = [pg for pg in range(good_k.shape[1]) if pg != own]
+    assert torch.equal(bits(good_k[:, others]), bits(bad_k[:, others])) and torch.equal(bits(good_v[:, others]), bits(bad_v[:, others]))
+    assert torch.equal(bits(before[0][:, own]), bits(bad_k[:, own])) and torch.equal(bits(before[1][:, own]), bits(bad_v[:, own]))
