@@ -41,14 +41,16 @@ PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 METRIC = "mixed-step throughput: embed tokens/s + decode tokens/s; %MFMA and %HBM peak"
 PROFILES = os.path.join(ROOT, "profiles")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_25405_amd", "csrc", f) for f in ("gemm.hip", "gemm_big.hip", "common.hpp")]
+# the projections' kernels, what they include, and the step, whose splits and row groups choose among them
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_25405_amd", "csrc", f)
+                  for f in ("gemm.hip", "gemm_big.hip", "gemm_big.hpp", "gemm_common.hpp", "common.hpp", "step.hip")]
 DATA = "synthetic (seeded N(0,0.02) weights and N(0,1) bf16 caches drawn on the device, uniform token ids)"
 GEMMS = ("gemm_qkv", "gemm_qkv_rope", "gemm_o", "gemm_gate_up", "gemm_down", "lm_head")
 
 
 def kernel_source_hash() -> str:
-    """SHA-256 of the GEMM kernel's sources with comments and whitespace removed: a change of
-    code invalidates a committed counter summary, a change of comments does not."""
+    """SHA-256 of the GEMM kernels' sources (KERNEL_SOURCES) with comments and whitespace removed: a
+    change of code invalidates a committed counter summary, a change of comments does not."""
     import hashlib
     import re
     h = hashlib.sha256()
