@@ -1,9 +1,10 @@
 // The large projections of the step (bf16, more than a few hundred rows): C[M][N] = A[M][K] *
 // W[N][K]^T on tiles of 256 rows x 256 weight rows, with the same epilogues as the small ones.
 //
-// What bounds them is power: at these sizes the chip holds its clock only as far as the energy of
-// the MFMAs, of the LDS reads and of the copies allows (ablated at 1024 x 28672 x 4096: MFMAs
-// alone 133 us, with their LDS reads 151 us, with the copies 187-198 us).  Hence:
+// What bounds them is the clock and the cycles without an MFMA.  The chip holds its clock only as far as the
+// energy of the MFMAs, of the LDS reads and of the copies allows (counters at 1024 x 28672 x 4096: 1.94 GHz
+// against 2.33 in row kernels, MFMA pipes busy 64 % of the cycles; ablated: MFMAs alone 133 us, with
+// their LDS reads 151 us, with the copies 187-198 us).  Hence:
 //  - v_mfma_f32_16x16x32_bf16 instead of 32x32x16: the same flops at half the accumulator
 //    traffic, 2.05 against 1.80 PFLOP/s in a stream of MFMAs on random operands (2.05 against
 //    1.82 GHz); two waves per SIMD, because one wave alone issues it every 19 cycles instead
