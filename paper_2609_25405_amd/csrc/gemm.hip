@@ -478,6 +478,21 @@ bool ring_split(int M, int N, int K, int splits) {
     return M > 128 && M <= 256 && blocks >= 192 && K / splits >= 2048;
 }
 
+}  // namespace
+
+// Whether gate/up beside another stream's launches (GemmArgs::wide 1, above 256 rows) takes this file's 192x256 tiles
+// instead of the light shapes of gemm_big.hip: where their rounds are shorter.  A K stage of a round of 256
+// workgroups lasts 1.4 us (7B, 370 rows 93.5 us in one round, 1088 rows 282 in three).  On the 7B shape that is 257 to 384
+// rows, for which the light shapes need two rounds of 192x128 tiles, in company 126 to 179 us against 102 to 156 (two
+// models, two layers: 320 + 16 rows 755 -> 710 us, 320 + 320 997 -> 935, 64 + 320 783 -> 732), and 641 to 768
+// (768 + 128 rows 1183 -> 1164, 768 + 256 1427 -> 1410); over 50 such steps of six shapes 1.6 % on average.
+bool gate_up_on_192(int M, int N, int K) {
+    const long tiles = (long)((M + 191) / 192) * ((N + 127) / 128);
+    return (tiles + 255) / 256 * (K / BK * 1.4 + 4.0) < plan_big(M, N, K, true, 1, true).us;
+}
+
+namespace {
+
 // Tile choice per shape, from measurements of the step's projections on MI355X (7B-class layer, cold
 // weights unless said otherwise):
 //  - M <= 64 (decode-only batches, the LM head): weight streaming; 64x64 tiles (more
@@ -497,7 +512,8 @@ bool ring_split(int M, int N, int K, int splits) {
 //    for that stream's small kernels (two models, 1024 + 256 rows, 8 layers: 6.08 against 5.99 ms).
 //    Groups of at most 896 rows (GemmArgs::wide 1) take its light shapes (two models, 4 layers, 512 +
 //    256 rows 2.58 -> 2.47 ms, 256 + 64 rows 1.43 -> 1.39 against this file's tiles; groups of at most 256
-//    rows as above, so on 128 or 144 KB of LDS where this file's tiles are the shorter alone); beside larger
+//    rows as above, so on 128 or 144 KB of LDS where this file's tiles are the shorter alone), gate/up on
+//    192x256 tiles of this file where their rounds are shorter (gate_up_on_192); beside larger
 //    groups (wide 2) this file's tiles stay: split-K projections of 129..256 rows and of more than
 //    896 on 256x256 (fewest workgroup-microseconds per flop; the other stream's launches fill the
 //    rest; the light shapes take 6.75 instead of 5.99 ms), gate/up above 256 rows on the 192x256,
@@ -509,6 +525,7 @@ hipError_t dispatch_bf16(const GemmArgs &a, hipStream_t s) {
         if (a.M <= 64) return run_bf16<64, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (a.M <= 128) return run_bf16<128, 128, 2, 2, EPI, 64, 4, 4, true>(a, s);
         if (big) {
+            if (a.wide && a.M > 256 && gate_up_on_192(a.M, a.N, a.K)) return run_bf16<192, 256, 2, 4, EPI>(a, s);
             const BigPlan p = plan_big(a.M, a.N, a.K, true, 1, a.wide);
             // (plan_big's estimate is for weights that several row tiles share; read once, from HBM, they
             // take a fifth longer: 160 / 256 rows of the 7B gate/up est. 57 / 65, measured 64 / 80 us)

@@ -1,6 +1,6 @@
 """The host side of the large bf16 projections: plan_big's covers against an exhaustive search written out
-here (every candidate's length computed, none skipped), and the cost of asking for a layer's covers
-again."""
+here (every candidate's length computed, none skipped), where gate/up beside another stream leaves them, and the cost
+of asking for a layer's covers again."""
 import ctypes
 import math
 import subprocess
@@ -95,6 +95,20 @@ def test_cover_is_the_exhaustive_one(N, K, swiglu, light):
             us, what = search(M, N, K, swiglu, splits, light)
             assert (p.shape, p.m_main, p.n_main, p.m_alt, p.n_alt, p.row_alt, p.col_alt) == what, (M, splits, us, p.us)
             assert p.splits == splits and p.us == pytest.approx(us, rel=1e-9)
+
+
+@pytest.mark.parametrize("N,K,spans", [(14336, 4096, [(257, 384), (641, 768)]), (13824, 5120, [(257, 384), (641, 768)]),
+                                       (8192, 2048, [(513, 768)]), (2816, 512, [])])
+def test_gate_up_beside_another_stream(N, K, spans):
+    """Gate/up of 257 to 896 rows beside another stream's launches: on 192x256 tiles, a round of which lasts 1.4 us a
+    stage, exactly where the light covers are longer (7B: two rounds of 192x128 tiles against one)."""
+    on_192 = P.load()["_ZN7orthrus14gate_up_on_192Eiii"]
+    on_192.restype, on_192.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    taken = [M for M in range(257, 897) if on_192(M, N, K)]
+    assert taken == [M for a, b in spans for M in range(a, b + 1)]
+    for M in range(257, 897):
+        rounds = math.ceil(math.ceil(M / 192) * math.ceil(N / 128) / 256)
+        assert (M in taken) == (rounds * (K // 64 * 1.4 + 4.0) < search(M, N, K, True, 1, True)[0])
 
 
 DRIVER = r"""

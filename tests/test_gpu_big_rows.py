@@ -4,11 +4,14 @@ counts that its covers give to 64-, 128- and 192-row tiles, a last row tile of o
 64, 128 and of 129 rows, whole tiles, and enough rows for several rounds; with LoRA adapters on part of the rows (ranks 16 and 48,
 so that a 32-column step of the update ends inside and past an adapter's block).  Each case names the K splits
 and covers that its four projections take, every cover of the kernel among them: a change of the rules
-that loses one shows here."""
+that loses one shows here.  Beside another model's launches, gate/up where it leaves the large kernel."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
+import paper_2609_25405_amd as P
 from tests.parity import Pair
 from tests.test_covers import covers
 from workload import Batch, DecodeRow, EmbChunk, ModelConfig, PagedKV, draw_tokens, make_lora, make_weights
@@ -66,4 +69,30 @@ def test_rows(rows, rank, d, ff, taken):
                   chunk_adapter=[(i % 3) - 1 for i in range(len(lens))] if rank else None)
     pair = Pair(cfg, W, kv)
     pair.workspace(rows, len(lens), n_dec, 64)
+    pair.step(batch)
+
+
+@pytest.mark.parametrize("rows,rank", [(257, 0), (384, 48), (513, 16), (768, 0)])
+def test_rows_beside_a_model(rows, rank):
+    """A step of two models whose embedding rows' gate/up takes 192x256 tiles beside the generator's launches: rows
+    ending inside a tile and at its end, adapters."""
+    on_192 = P.load()["_ZN7orthrus14gate_up_on_192Eiii"]
+    on_192.restype, on_192.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    ff = 14080
+    assert on_192(rows, ff, 512)
+    cfg = ModelConfig(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=ff, vocab=512, dtype="bf16")
+    W, G = make_weights(cfg, 11, model_tag=1), make_weights(cfg, 12, model_tag=2)
+    if rank:
+        W["adapters"] = [make_lora(cfg, 5, rank, tag=i) for i in range(2)]
+    kv, gkv = PagedKV(cfg, rows // 16 + 4, 2, 64, 3), PagedKV(cfg, 12, 3, 4, 4)
+    lens = [rows // 2, rows - rows // 2]
+    for j, n in enumerate(lens):
+        kv.reserve(j, n)
+    for j in range(3):
+        gkv.fill_random(j, 9 + 16 * j, 5)
+        gkv.reserve(j, 10 + 16 * j)
+    batch = Batch([EmbChunk(j, 0, n, True, "mean") for j, n in enumerate(lens)], [DecodeRow(j, 9 + 16 * j) for j in range(3)],
+                  draw_tokens(8, 0, rows + 3, cfg.vocab), chunk_adapter=[1, -1] if rank else None)
+    pair = Pair(cfg, W, kv, cfg, G, gkv)
+    pair.workspace(rows + 3, 2, 3, 60)
     pair.step(batch)
