@@ -1,4 +1,4 @@
-// Projections of at most 16 rows through small weights (bf16; skinny_takes): a few rows of a small model,
+// Projections of at most 16 rows (QKV: 128) through small weights (bf16; skinny_takes): a few rows of a small model,
 // where a launch is a chain of latencies and a step a chain of launches.  Hence no LDS staging and
 // no split-K slabs: a workgroup takes 16 weight rows (two sets of 16 where an epilogue needs
 // pairs: gate and up, the two halves of a rotation), its eight waves split K, and each wave loads its
@@ -29,6 +29,20 @@ __global__ __launch_bounds__(64 * kWaves) void skinny_kernel(SkinnyArgs a) {
     __shared__ float inv_rms[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half_hd = a.rope.hd / 2;
+    if constexpr (EPI == SKINNY_QKV) {
+        if (blockIdx.y > 0) {               // this workgroup's 16 rows
+            const int m0 = blockIdx.y * kSkinnyRows;
+            if (NORM) a.x += (size_t)m0 * a.K;
+            else a.A = (const char *)a.A + (size_t)m0 * a.lda * 2;
+            a.M -= m0;
+            a.rope.pos += m0;
+            a.rope.seq += m0;
+            a.rope.cs += (size_t)m0 * half_hd;
+            a.rope.q_out = (bf16 *)a.rope.q_out + (size_t)m0 * a.rope.nq * a.rope.hd;
+            a.rope.Te -= m0;
+        }
+        a.M = min(a.M, kSkinnyRows);
+    }
     // first weight row of each set
     int n0[SETS];
     if constexpr (EPI == SKINNY_QKV) {
@@ -183,8 +197,9 @@ __global__ __launch_bounds__(64 * kWaves) void skinny_kernel(SkinnyArgs a) {
 
 template <int EPI, int SETS>
 hipError_t go(const SkinnyArgs &a, int blocks, hipStream_t s) {
+    const int row_tiles = (a.M + kSkinnyRows - 1) / kSkinnyRows;
     auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * kWaves), 0, s, a);
+        hipLaunchKernelGGL(kernel, dim3(blocks, row_tiles), dim3(64 * kWaves), 0, s, a);
         return hipGetLastError();
     };
     if constexpr (EPI == SKINNY_SWIGLU || EPI == SKINNY_QKV) {
@@ -201,9 +216,20 @@ bool skinny_takes(int M, int weight_rows, int K) {
     return M <= kSkinnyRows && K % 32 == 0 && (size_t)weight_rows * K * 2 <= (size_t)(M <= 4 ? 16 : 4) << 20;
 }
 
+// QKV of 17 to 128 rows, whose rotation and append else are a launch of their own: 16 rows a workgroup, so each row
+// tile reads the weights again, from L2.  Worth it while these reads are at most 28 MB: 512-wide, 6 layers, 17 rows 259 ->
+// 234 us, 128 rows 371 -> 326; 1024-wide (3 MB) 128 rows 416 -> 394; 2048-wide (4 MB) 64 rows 414 -> 389; two models, 512-wide, 4
+// layers, where the host's launches bound the step, 20 + 20 rows 283 -> 253.  At 38 MB equal or 4 to 7 % slower, at
+// 75 MB 4 to 9 %.
+bool skinny_takes_qkv(int M, int weight_rows, int K) {
+    const size_t row_tiles = (M + kSkinnyRows - 1) / kSkinnyRows;
+    return skinny_takes(M, weight_rows, K) ||
+           (M <= kSkinnyQkvRows && K % 32 == 0 && (size_t)weight_rows * K * 2 * row_tiles <= (size_t)28 << 20);
+}
+
 hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
-    if (a.M > kSkinnyRows || a.K % 32 || (a.b_blocked && (epilogue != SKINNY_STORE || a.K % 64)) || (!a.A && epilogue != SKINNY_SWIGLU && epilogue != SKINNY_QKV))
+    if (a.M > (epilogue == SKINNY_QKV ? kSkinnyQkvRows : kSkinnyRows) || a.K % 32 || (a.b_blocked && (epilogue != SKINNY_STORE || a.K % 64)) || (!a.A && epilogue != SKINNY_SWIGLU && epilogue != SKINNY_QKV))
         return hipErrorInvalidValue;
     switch (epilogue) {
         case SKINNY_STORE: return go<SKINNY_STORE, 2>(a, (a.N + 31) / 32, s);

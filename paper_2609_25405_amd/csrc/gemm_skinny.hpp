@@ -5,7 +5,7 @@
 
 namespace orthrus {
 
-constexpr int kSkinnyRows = 16;
+constexpr int kSkinnyRows = 16, kSkinnyQkvRows = 128;
 
 enum SkinnyEpilogue { SKINNY_STORE = 0, SKINNY_ADD, SKINNY_SWIGLU, SKINNY_QKV };
 
@@ -21,9 +21,10 @@ struct SkinnyArgs {
     // (rope.qkv unused; rope.pos, seq, cs and q_out start at the launch's first row)
     RopeArgs rope;
 };
-// bf16; M <= kSkinnyRows, K % 32 == 0
+// bf16; M <= kSkinnyRows (SKINNY_QKV: kSkinnyQkvRows), K % 32 == 0
 hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s);
 // whether the launch belongs here rather than on the tiled kernels (bf16; weight rows of K each)
 bool skinny_takes(int M, int weight_rows, int K);
+bool skinny_takes_qkv(int M, int weight_rows, int K);      // the same for SKINNY_QKV
 
 }  // namespace orthrus

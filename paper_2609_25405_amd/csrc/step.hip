@@ -638,11 +638,12 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
         return combine ? launch_attn_combine(dt, ag, n_dec, groups[gi].st) : launch_attention(dt, ag, groups[gi].st);
     };
 
-    // Projections of gemm_skinny.hip (bf16, no adapters, every row group of at most kSkinnyRows rows):
+    // Projections of gemm_skinny.hip (bf16, no adapters, every row group of few rows):
     // they finish their rows themselves (residual add, rotation and append), so no slabs of
     // theirs are pending, and where no other projection's are they also norm the rows of x
-    auto skinny = [&](int N, int K) { return dt == ORTHRUS_BF16 && p.n_used == 0 && skinny_takes(max_rows, N, K); };
-    const bool sk_qkv = skinny(qkvd, d), sk_o = skinny(d, qd), sk_gu = skinny(2 * F, d), sk_down = skinny(d, F);
+    const bool few = dt == ORTHRUS_BF16 && p.n_used == 0;
+    auto skinny = [&](int N, int K) { return few && skinny_takes(max_rows, N, K); };
+    const bool sk_qkv = few && skinny_takes_qkv(max_rows, qkvd, d), sk_o = skinny(d, qd), sk_gu = skinny(2 * F, d), sk_down = skinny(d, F);
     auto skinny_args = [&](const Group &g, const void *A, int lda, const void *B0, int N, int K) {
         SkinnyArgs sa{};
         sa.A = (const char *)A + (size_t)g.r0 * lda * es;

@@ -1,5 +1,6 @@
 """Steps of at most 16 rows per model through small weights (the projections of gemm_skinny.hip) against
-the float64 oracle: 1, 4, 5, 16 rows and, past the rule, 17; head_dim 64 and 128 (two and four
+the float64 oracle: 1, 4, 5, 16 rows and, past the rule, 17; QKV alone of 17 to 128 rows (tiles of 16: a last tile of
+one row, whole ones, pools and models that change inside one; rows it norms itself) and past its rule; head_dim 64 and 128 (two and four
 16-dim parts of a rotation half); K that does not divide over the eight waves (768); K of several rounds of
 loads, ending inside one (down of 4864: 19 steps a wave, two rounds of 16; rows normed in the launch, 2304:
 9 steps, two rounds of 8); rows normed in the launch, with the gather (layer 0), and by a launch of
@@ -40,7 +41,8 @@ LARGE_O = config(512, 64, 16, 128, 256)     # o: 8 MB of weights, too much for m
     (NARROW, 0, 0, 1, False), (NARROW, 0, 0, 4, False), (NARROW, 7, 4, 5, False), (NARROW, 0, 0, 17, False),
     (ODD, 1, 2, 2, False), (ODD, 6, 0, 10, True), (WIDE, 0, 0, 4, False), (WIDE, 3, 3, 10, False),
     (DEEP, 0, 0, 4, False), (DEEP, 1, 0, 2, False), (DEEP_NORMED, 0, 0, 3, False), (DEEP_NORMED, 3, 2, 2, False),
-    (LARGE_O, 0, 0, 7, False)])
+    (LARGE_O, 0, 0, 7, False), (NARROW, 0, 0, 33, False), (NARROW, 30, 50, 48, False), (NARROW, 0, 0, 129, False),
+    (ODD, 20, 10, 11, False), (ODD, 70, 5, 31, True), (ODD, 17, 0, 64, True)])
 def test_few_rows(cfg, emb, prompt, rows, two):
     W = make_weights(cfg, 31, model_tag=1)
     n0 = (1 if emb else 0)
@@ -66,36 +68,55 @@ def test_few_rows(cfg, emb, prompt, rows, two):
     pair.step(batch)
 
 
-def test_bad_page():
+@pytest.mark.parametrize("ahead", [0, 17])
+def test_bad_page(ahead):
     """The launch that appends flags the row whose page is past the pool and writes nothing for it; the other
     rows and every other slot are as in a run with its page in place."""
     cfg = NARROW
     W = make_weights(cfg, 31)
-    ctx = [40, 33, 7]
+    ctx = [7] * ahead + [40, 33, 7]
+    n, row = len(ctx), ahead + 1
     results = []
     for bad in (False, True):
-        kv = PagedKV(cfg, 20, 3, 4, 8)
+        kv = PagedKV(cfg, 20 + ahead, n, 4, 8)
         for j, c in enumerate(ctx):
             kv.fill_random(j, c, 4)
             kv.reserve(j, c + 1)
         dm, dkv = R.DeviceModel(cfg, W), R.DeviceKV.from_paged(kv)
         bt = kv.block_table.copy()
-        own = int(bt[1, 2])
+        own = int(bt[row, 2])
         if bad:
-            bt[1, 2] = kv.n_pages
+            bt[row, 2] = kv.n_pages
         dkv.set_block_table(bt)
         before = [dkv.k.clone(), dkv.v.clone()]
-        ws = R.Workspace(dm, dm, 3, 0, 3, 64)
-        logits = torch.zeros((3, cfg.vocab), device="cuda")
-        R.step(dm, dm, Batch([], [DecodeRow(j, c) for j, c in enumerate(ctx)], draw_tokens(6, 0, 3, cfg.vocab)), dkv, dkv, None, None,
+        ws = R.Workspace(dm, dm, n, 0, n, 64)
+        logits = torch.zeros((n, cfg.vocab), device="cuda")
+        R.step(dm, dm, Batch([], [DecodeRow(j, c) for j, c in enumerate(ctx)], draw_tokens(6, 0, n, cfg.vocab)), dkv, dkv, None, None,
                logits, None, ws)
         torch.cuda.synchronize()
         assert ws.device_error() == (A.ORTHRUS_DEVERR_PAGE if bad else 0)
         results.append((logits, dkv.k, dkv.v, before))
     (good_l, good_k, good_v, _), (bad_l, bad_k, bad_v, before) = results
     assert torch.isfinite(bad_l).all()
-    assert torch.equal(good_l[[0, 2]], bad_l[[0, 2]])
+    others_l = [j for j in range(n) if j != row]
+    assert torch.equal(good_l[others_l], bad_l[others_l])
     bits = lambda t: t.view(torch.int16)
     others = [pg for pg in range(good_k.shape[1]) if pg != own]
     assert torch.equal(bits(good_k[:, others]), bits(bad_k[:, others])) and torch.equal(bits(good_v[:, others]), bits(bad_v[:, others]))
     assert torch.equal(bits(before[0][:, own]), bits(bad_k[:, own])) and torch.equal(bits(before[1][:, own]), bits(bad_v[:, own]))
+
+
+@pytest.mark.parametrize("rows", [17, 128])
+def test_rotation_is_no_launch_of_its_own(rows):
+    cfg = NARROW
+    kv = PagedKV(cfg, rows + 2, rows, 1, 8)
+    for j in range(rows):
+        kv.reserve(j, 1)
+    dm, dkv = R.DeviceModel(cfg, make_weights(cfg, 31)), R.DeviceKV.from_paged(kv)
+    ws = R.Workspace(dm, dm, rows, 0, rows, 2)
+    R.profile_begin(dm)
+    R.step(dm, dm, Batch([], [DecodeRow(j, 0) for j in range(rows)], draw_tokens(6, 0, rows, cfg.vocab)), dkv, dkv, None, None,
+           torch.zeros((rows, cfg.vocab), device="cuda"), None, ws)
+    torch.cuda.synchronize()
+    names = R.profile_end(dm)
+    assert "gemm_qkv_rope" in names and "rope_append" not in names, names
