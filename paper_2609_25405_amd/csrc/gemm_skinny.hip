@@ -4,13 +4,14 @@
 // pairs: gate and up, the two halves of a rotation), its eight waves split K, and each wave loads its
 // operands straight into registers in the layout of v_mfma_f32_16x16x32_bf16, up to sixteen K
 // steps ahead.  The eight partial tiles meet in LDS and are summed in wave order, and the
-// epilogues finish the row: residual add, SwiGLU, rotation with the cache append.  The launch also norms
-// complete rows of x itself, under the first weights' latency: each workgroup reads all rows twice for it,
-// from L2, at most 8.4 MB at the sizes skinny_takes allows, a microsecond beside a norm launch of 3 to 5 us.  4 rows of a 512-wide 8-layer model: 8 launches a layer -> 5 and a step 364 -> 227
+// epilogues finish the row: residual add, SwiGLU, rotation with the cache append.  The launch may also norm
+// complete rows of x itself (skinny_norms), under the first weights' latency.  4 rows of a 512-wide 8-layer model: 8 launches a layer -> 5 and a step 364 -> 227
 // us (projections 5.5 to 10.4 us on the tiled kernels, 3.7 to 5.7 here).
 //
 // Larger weights stay on the tiled kernels, whose copies to LDS move whole 128-byte lines: one row of
 // the 7B shape takes 52 us here against 45 for gate/up, 37.8 against 28.7 for o and down.
+#include <algorithm>
+
 #include "gemm_common.hpp"
 #include "gemm_skinny.hpp"
 
@@ -19,12 +20,14 @@ namespace orthrus {
 namespace {
 
 constexpr int kWaves = 8;
+constexpr int kNormK = 1024;      // the longest rows normed here
 
 // SETS: weight row sets of 16 per workgroup.  NORM: A is x normed here.
 template <int EPI, int SETS, bool NORM>
 __global__ __launch_bounds__(64 * kWaves) void skinny_kernel(SkinnyArgs a) {
-    // K steps of weights in flight; a normed row takes four times the registers of a bf16 one
-    constexpr int kAhead = NORM ? 4 : 8;
+    // K steps of weights in flight per register set; a normed row, which takes four times the registers of a bf16
+    // one, has all its steps in one (K <= kNormK)
+    constexpr int kAhead = NORM ? kNormK / (32 * kWaves) : 8, kLoads = NORM ? 1 : 2;
     __shared__ float red[kWaves][SETS][16][17];
     __shared__ float inv_rms[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(64 * kWaves) void skinny_kernel(SkinnyArgs a) {
     auto w_at = [&](int f, int s) {
         return wp[f] + (a.b_blocked ? (size_t)(s >> 1) * 8192 + (s & 1) * 64 : (size_t)s * 64);
     };
-    bf16x8 w[2][kAhead][SETS];
+    bf16x8 w[kLoads][kAhead][SETS];
     auto load_weights = [&](int s, int set) {
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
@@ -144,11 +147,15 @@ __global__ __launch_bounds__(64 * kWaves) void skinny_kernel(SkinnyArgs a) {
             for (int f = 0; f < SETS; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[set][i][f], av[i], acc[f], 0, 0, 0);
         }
     };
-    for (int s = s0; s < s1; s += 2 * kAhead) {
-        load_weights(s + kAhead, 1);
-        multiply(s, 0);
-        load_weights(s + 2 * kAhead, 0);
-        multiply(s + kAhead, 1);
+    if constexpr (NORM) {
+        multiply(s0, 0);
+    } else {
+        for (int s = s0; s < s1; s += 2 * kAhead) {
+            load_weights(s + kAhead, 1);
+            multiply(s, 0);
+            load_weights(s + 2 * kAhead, 0);
+            multiply(s + kAhead, 1);
+        }
     }
     // lane holds activation row lane % 16, weight rows 4 (lane / 16) + r of each set
 #pragma unroll
@@ -227,9 +234,15 @@ bool skinny_takes_qkv(int M, int weight_rows, int K) {
            (M <= kSkinnyQkvRows && K % 32 == 0 && (size_t)weight_rows * K * 2 * row_tiles <= (size_t)28 << 20);
 }
 
+// Every workgroup sums the squares of its rows, two rows a wave with 16 and a load a 256 columns each, and reads them a second
+// time as fp32: worth the norm's launch of 4 us while it is short.  Steps of 6 layers, normed here against by a launch:
+// 512-wide, 1 / 8 / 16 rows 133 / 148 / 167 us against 149 / 161 / 170; 1024-wide, 1 / 8 / 16 rows 154 / 171 / 200
+// against 160 / 172 / 182; 1536-wide, 1 row 179 against 175; 4096-wide, 1 / 16 rows 297 / 428 against 245 / 295.
+bool skinny_norms(int M, int K) { return K <= kNormK && std::min(M, kSkinnyRows) * K <= 8192; }
+
 hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
-    if (a.M > (epilogue == SKINNY_QKV ? kSkinnyQkvRows : kSkinnyRows) || a.K % 32 || (a.b_blocked && (epilogue != SKINNY_STORE || a.K % 64)) || (!a.A && epilogue != SKINNY_SWIGLU && epilogue != SKINNY_QKV))
+    if (a.M > (epilogue == SKINNY_QKV ? kSkinnyQkvRows : kSkinnyRows) || a.K % 32 || (a.b_blocked && (epilogue != SKINNY_STORE || a.K % 64)) || (!a.A && (a.K > kNormK || (epilogue != SKINNY_SWIGLU && epilogue != SKINNY_QKV))))
         return hipErrorInvalidValue;
     switch (epilogue) {
         case SKINNY_STORE: return go<SKINNY_STORE, 2>(a, (a.N + 31) / 32, s);

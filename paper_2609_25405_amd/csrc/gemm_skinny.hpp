@@ -26,5 +26,7 @@ hipError_t launch_skinny(int epilogue, const SkinnyArgs &a, hipStream_t s);
 // whether the launch belongs here rather than on the tiled kernels (bf16; weight rows of K each)
 bool skinny_takes(int M, int weight_rows, int K);
 bool skinny_takes_qkv(int M, int weight_rows, int K);      // the same for SKINNY_QKV
+// whether the launch also norms complete rows of x itself
+bool skinny_norms(int M, int K);
 
 }  // namespace orthrus

@@ -640,7 +640,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
 
     // Projections of gemm_skinny.hip (bf16, no adapters, every row group of few rows):
     // they finish their rows themselves (residual add, rotation and append), so no slabs of
-    // theirs are pending, and where no other projection's are they also norm the rows of x
+    // theirs are pending, and where no other projection's are and it pays they also norm the rows of x
     const bool few = dt == ORTHRUS_BF16 && p.n_used == 0;
     auto skinny = [&](int N, int K) { return few && skinny_takes(max_rows, N, K); };
     const bool sk_qkv = few && skinny_takes_qkv(max_rows, qkvd, d), sk_o = skinny(d, qd), sk_gu = skinny(2 * F, d), sk_down = skinny(d, F);
@@ -671,7 +671,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
 
     for (int l = 0; l < c.n_layers; ++l) {
         // layer 0's rows were normed with the gather
-        const bool qkv_norms = l > 0 && sk_qkv && pending == 0;
+        const bool qkv_norms = l > 0 && sk_qkv && pending == 0 && skinny_norms(max_rows, d);
         if (l > 0) SYNC_GROUPS(norm_rows(qkv_norms, [&](const Group &g) { return g.m->layers[l].attn_norm; }));
         ra.k_cache[0] = (char *)emb_kv->k_cache + l * e_stride;
         ra.v_cache[0] = (char *)emb_kv->v_cache + l * e_stride;
@@ -763,7 +763,7 @@ int step_impl(const orthrus_model *emb, const orthrus_model *gen, const orthrus_
             return ORTHRUS_OK;
         };
         SYNC_GROUPS(add_rows("gemm_o", sk_o, 1, ob, qd, [](const orthrus_layer_weights &lw) { return lw.w_o; }));
-        const bool gu_norms = sk_gu && pending == 0;
+        const bool gu_norms = sk_gu && pending == 0 && skinny_norms(max_rows, d);
         SYNC_GROUPS(norm_rows(gu_norms, [&](const Group &g) { return g.m->layers[l].mlp_norm; }));
         for (int gi = 0; gi < n_groups; ++gi) {
             const Group &g = groups[gi];

@@ -2,9 +2,9 @@
 the float64 oracle: 1, 4, 5, 16 rows and, past the rule, 17; QKV alone of 17 to 128 rows (tiles of 16: a last tile of
 one row, whole ones, pools and models that change inside one; rows it norms itself) and past its rule; head_dim 64 and 128 (two and four
 16-dim parts of a rotation half); K that does not divide over the eight waves (768); K of several rounds of
-loads, ending inside one (down of 4864: 19 steps a wave, two rounds of 16; rows normed in the launch, 2304:
-9 steps, two rounds of 8); rows normed in the launch, with the gather (layer 0), and by a launch of
-their own before gate/up (an o projection whose weights are too large leaves partial sums); prompt rows,
+loads, ending inside one (down of 4864: 19 steps a wave, two rounds of 16; QKV of 2304: 9); rows normed in the launch (K
+of 256 to 1024: one to four steps a wave, up to 8192 values in all), with the gather (layer 0), and by a launch of
+their own (past that, and before gate/up where an o projection whose weights are too large leaves partial sums); prompt rows,
 embedding rows and decode rows together; a vocabulary that ends inside a set of 16; two models; a
 row whose page is not in the pool."""
 import pytest
@@ -33,16 +33,19 @@ NARROW = config(512, 8, 2, 128, 2816)
 ODD = config(768, 12, 12, 64, 768)
 WIDE = config(2048, 4, 2, 128, 512)
 DEEP = config(512, 8, 2, 128, 4864)
-DEEP_NORMED = config(2304, 2, 1, 128, 256)
+WIDEST = config(2304, 2, 1, 128, 256)
+NORMED = config(1024, 4, 2, 128, 512)
+SMALL = config(256, 4, 4, 64, 512)
 LARGE_O = config(512, 64, 16, 128, 256)     # o: 8 MB of weights, too much for more than 4 rows
 
 
 @pytest.mark.parametrize("cfg,emb,prompt,rows,two", [
     (NARROW, 0, 0, 1, False), (NARROW, 0, 0, 4, False), (NARROW, 7, 4, 5, False), (NARROW, 0, 0, 17, False),
     (ODD, 1, 2, 2, False), (ODD, 6, 0, 10, True), (WIDE, 0, 0, 4, False), (WIDE, 3, 3, 10, False),
-    (DEEP, 0, 0, 4, False), (DEEP, 1, 0, 2, False), (DEEP_NORMED, 0, 0, 3, False), (DEEP_NORMED, 3, 2, 2, False),
+    (DEEP, 0, 0, 4, False), (DEEP, 1, 0, 2, False), (WIDEST, 0, 0, 3, False), (WIDEST, 3, 2, 2, False),
     (LARGE_O, 0, 0, 7, False), (NARROW, 0, 0, 33, False), (NARROW, 30, 50, 48, False), (NARROW, 0, 0, 129, False),
-    (ODD, 20, 10, 11, False), (ODD, 70, 5, 31, True), (ODD, 17, 0, 64, True)])
+    (ODD, 20, 10, 11, False), (ODD, 70, 5, 31, True), (ODD, 17, 0, 64, True), (NORMED, 0, 0, 8, False),
+    (NORMED, 3, 2, 4, True), (NORMED, 0, 0, 9, False), (SMALL, 0, 0, 16, False), (SMALL, 5, 3, 40, False)])
 def test_few_rows(cfg, emb, prompt, rows, two):
     W = make_weights(cfg, 31, model_tag=1)
     n0 = (1 if emb else 0)
@@ -120,3 +123,20 @@ def test_rotation_is_no_launch_of_its_own(rows):
     torch.cuda.synchronize()
     names = R.profile_end(dm)
     assert "gemm_qkv_rope" in names and "rope_append" not in names, names
+
+
+@pytest.mark.parametrize("cfg,rows,launches", [(NARROW, 4, 1), (NARROW, 16, 3), (NORMED, 8, 1), (NORMED, 9, 4), (WIDE, 1, 4)])
+def test_norms_in_the_launch_where_rows_are_short(cfg, rows, launches):
+    """Launches of norms in two layers and after them: the gather's alone where the projections norm their rows
+    (gate and up of 16 rows of the 512-wide model are too large)."""
+    kv = PagedKV(cfg, rows + 2, rows, 1, 8)
+    for j in range(rows):
+        kv.reserve(j, 1)
+    dm, dkv = R.DeviceModel(cfg, make_weights(cfg, 31)), R.DeviceKV.from_paged(kv)
+    ws = R.Workspace(dm, dm, rows, 0, rows, 2)
+    R.profile_begin(dm)
+    R.step(dm, dm, Batch([], [DecodeRow(j, 0) for j in range(rows)], draw_tokens(6, 0, rows, cfg.vocab)), dkv, dkv, None, None,
+           torch.zeros((rows, cfg.vocab), device="cuda"), None, ws)
+    torch.cuda.synchronize()
+    names = R.profile_end(dm)
+    assert sum(names[n][0] for n in names if "rmsnorm" in n or n == "gather_norm") == launches, names
